@@ -348,6 +348,31 @@ jf_status jf_prefill_attn_q4(const jf_kv_layout* layout,
                              int32_t prefix_len, float softmax_scale,
                              void* out, hipStream_t stream);
 
+/* jf_prefill_attn_q4 with device scratch that lets the work be laid evenly
+ * over the chip: where the chunk's rows alone would not fill it (a short
+ * chunk over a long prefix) or would leave its last turn nearly empty, the
+ * keys of a KV head are shared evenly by its blocks, which leave fp32 partial
+ * states (o, m, l) in the workspace for a second small kernel to combine.
+ * jf_prefill_workspace_bytes gives the bytes such a call needs: 0 where the
+ * work is even as it is (the workspace is then not used and may be NULL), and
+ * never more than two partial states per compute unit, whatever the lengths
+ * (73 MB at head_dim 128, 147 MB at 256).
+ *   workspace  device scratch, 16-byte aligned, of at least that many bytes;
+ *              its contents do not matter before the call nor after it.  Calls
+ *              that may overlap in time must not share one.
+ * Other arguments, outputs and errors as jf_prefill_attn_q4; the outputs are
+ * the same up to the order of the fp32 sums. */
+jf_status jf_prefill_workspace_bytes(const jf_kv_layout* layout, int32_t T,
+                                     int32_t num_q_heads, int32_t prefix_len, size_t* bytes);
+jf_status jf_prefill_attn_q4_ws(const jf_kv_layout* layout,
+                                const jf_kv_pool_ptrs* pool, const void* q,
+                                const void* k_chunk, const void* v_chunk,
+                                int32_t T, int32_t num_q_heads,
+                                const int32_t* block_table, int32_t max_pages,
+                                int32_t prefix_len, float softmax_scale,
+                                void* workspace, size_t workspace_bytes,
+                                void* out, hipStream_t stream);
+
 /* Page -> operand reconstruction of one head group for an SDPA-style
  * consumer (Background, "Stored format is not execution format", eq.
  * layerbytes; Sec. 3.1, "Finish one head group before starting the next",

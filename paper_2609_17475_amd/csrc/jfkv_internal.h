@@ -90,6 +90,17 @@ hipError_t launch_prefill(const jf_kv_layout& L, const jf_kv_pool_ptrs& pool,
                           int32_t prefix_len, float softmax_scale, void* out,
                           hipStream_t stream);
 
+// Argument checks of the prefill entry points (which sit beside the kernel's
+// work plan), and the status of a message or of a launch.
+jf_status check_prefill(const jf_kv_layout* layout, const jf_kv_pool_ptrs* pool, const void* q,
+                        const void* k_chunk, const void* v_chunk, int32_t T, int32_t num_q_heads,
+                        const int32_t* block_table, int32_t max_pages, int32_t prefix_len,
+                        float softmax_scale, const void* out);
+jf_status check_prefill_shape(const jf_kv_layout* layout, int32_t T, int32_t num_q_heads,
+                              int32_t prefix_len);
+jf_status status_invalid(const char* message);
+jf_status status_of(hipError_t e, const char* what);
+
 hipError_t launch_tq4_encode(const jf_kv_layout& L, void* words, void* norms, const void* x,
                              const float* signs, const float* centroids, const int32_t* cu_tok,
                              const int32_t* start_pos, const int32_t* block_tables, int32_t B,

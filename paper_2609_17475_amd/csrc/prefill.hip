@@ -36,7 +36,9 @@
 // (exact but for the last bit of a subnormal), with no low part.
 //
 // Block = 8 waves sharing KV head kv, 32 query rows per wave (16 at d = 256); a row is
-// (chunk position i, query head h of kv), position-major.  Per 64-key tile:
+// (chunk position i, query head h of kv), position-major.  A block has one row
+// block, or (see PrefillPlan) an even share of its KV head's tiles whatever
+// row blocks they belong to.  Per 64-key tile:
 //   S^T = K Q^T      (A = K code tile [key][dim] from LDS, B = Q^T in
 //                     registers, per scale group; a lane holds one query
 //                     column, 4 keys per 16-key tile, so row max and sum
@@ -55,7 +57,37 @@
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "jfkv_internal.h"
+
+namespace jfkv {
+
+// Key tiles of the row blocks of one KV head in turn: block rb (rows rb * rows
+// .. of (position, query head) rows) has the prefix's n_pre tiles and those of
+// the chunk up to its last position.  Its last row over gq * kt is carried as
+// quotient and remainder, so stepping needs no division.
+struct RowBlockTiles {
+  int n_pre, last, q, r, dq, dr, u;
+  __host__ __device__ RowBlockTiles(int rows, int T, int gq, int n_pre_, int kt)
+      : n_pre(n_pre_), last((T - 1) / kt), u(gq * kt) {
+    q = (rows - 1) / u;
+    r = (rows - 1) % u;
+    dq = rows / u;
+    dr = rows % u;
+  }
+  __host__ __device__ int tiles() const { return n_pre + 1 + (q < last ? q : last); }
+  __host__ __device__ void next() {
+    q += dq;
+    r += dr;
+    if (r >= u) {
+      r -= u;
+      ++q;
+    }
+  }
+};
+
+}  // namespace jfkv
 
 namespace {
 
@@ -127,14 +159,34 @@ __device__ __forceinline__ f32x4 mfma(h8 a, h8 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
 }
 
-template <int D, int G>
+// four output elements acc * inv as fp16
+__device__ __forceinline__ void store_o4(__half* dst, f32x4 acc, float inv) {
+  uint2 v;
+  v.x = __builtin_bit_cast(uint32_t, __floats2half2_rn(acc[0] * inv, acc[1] * inv));
+  v.y = __builtin_bit_cast(uint32_t, __floats2half2_rn(acc[2] * inv, acc[3] * inv));
+  *reinterpret_cast<uint2*>(dst) = v;
+}
+
+// fp32 words of a part of a row block in the workspace: per wave the output
+// accumulators ([dim tile][row tile][lane] of four), then (maximum, sum)
+// ([row tile][lane])
+template <int D>
+constexpr int part_floats() { return kWaves * row_tiles<D>() * 64 * (D / 4 + 2); }
+
+// PRE: the call has a prefix.  Without one (the first chunk of a prompt) no
+// tile is rebuilt from codes, so the registers of that hold the chunk rows of
+// the tile after the next, and LDS no low parts; G is then only how the
+// scores are summed.  (Staged without the fetch ahead, in the kernel for both,
+// 2,048 rows of 32/8 heads took 121 us, and 81 us here: the loads' latency was
+// paid for each tile.)
+template <int D, int G, bool PRE>
 __global__ __launch_bounds__(64 * kWaves) void prefill_kernel(
     const uint8_t* __restrict__ k_codes, const uint32_t* __restrict__ k_meta,
     const uint8_t* __restrict__ v_codes, const uint32_t* __restrict__ v_meta,
     const __half* __restrict__ q, const __half* __restrict__ k_chunk,
     const __half* __restrict__ v_chunk, const int32_t* __restrict__ block_table,
-    __half* __restrict__ out, int T, int Hq, int Hkv, int P, int NP, int prefix_len,
-    float scale_log2) {
+    __half* __restrict__ out, float* __restrict__ ws, int T, int Hq, int Hkv, int P, int NP,
+    int prefix_len, float scale_log2, int n_blk, int head_tiles) {
   constexpr int NR = row_tiles<D>();
   constexpr int kThreads = 64 * kWaves;
   constexpr int kRowsPerWave = 16 * NR;
@@ -165,18 +217,32 @@ __global__ __launch_bounds__(64 * kWaves) void prefill_kernel(
   static_assert(NBQ < 3, "lane group 3 carries the running maximum");
   __shared__ __attribute__((aligned(16))) uint32_t sKb[2][KT][4][4];
   __shared__ __attribute__((aligned(16))) _Float16 sV[2][D][VP];   // V^ / 2, high part
-  __shared__ __attribute__((aligned(16))) _Float16 sVl[2][D][VP];  // low part (prefix tiles)
+  __shared__ __attribute__((aligned(16))) _Float16 sVl[PRE ? 2 : 1][PRE ? D : 1][VP];  // low part (prefix tiles)
 
   // KV head fastest: the blocks of one KV head land on one XCD (round-robin
   // dispatch over the 8 XCDs), so its tiles are shared in that XCD's L2.
   const int kv = blockIdx.x % Hkv;
-  const int rb = blockIdx.x / Hkv;
+  const int blk = blockIdx.x / Hkv;
   const int gq = Hq / Hkv;
-  const int r0 = rb * kRows;
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   const int l16 = lane & 15, q4 = lane >> 4;
   const size_t head_codes = (size_t)P * (D / 2);
+  const int n_pre = PRE ? (prefix_len + KT - 1) / KT : 0;
+
+  // The block's tiles: those of row block blk, or (a split call: ws) its share
+  // of all the tiles of its KV head, row block after row block (the head's
+  // tiles dealt evenly to n_blk blocks); rb, j0: the first one.  (One kernel
+  // for both: with the split a template argument, the whole-row-block instance
+  // came out 8 % slower, 3.51 against 3.20 ms for 2,048 rows over 65,536.)
+  int rb = blk, j0 = 0;
+  int left = 1;  // tiles of the share from (rb, j0) on
+  if (ws) {
+    j0 = blk * head_tiles / n_blk;
+    left = (blk + 1) * head_tiles / n_blk - j0;
+    jfkv::RowBlockTiles rbt(kRows, T, gq, n_pre, KT);
+    for (rb = 0; j0 >= rbt.tiles(); rbt.next(), ++rb) j0 -= rbt.tiles();
+  }
 
   // scores are scaled by |scale| (log2 units) in the exponent; a negative
   // scale negates the query instead (exact).  A positive floor keeps masked
@@ -184,65 +250,12 @@ __global__ __launch_bounds__(64 * kWaves) void prefill_kernel(
   const float cabs = fmaxf(fabsf(scale_log2), 1e-30f);
   const _Float16 qsgn = scale_log2 < 0.0f ? (_Float16)-1.0f : (_Float16)1.0f;
 
-  // ---- Q^T operands (exact fp16, dims in K^ storage order)
+  // per row block: Q^T operands (exact fp16, dims in K^ storage order)
   h8 qb[NR][KSTEPS];
   // bias-product operand: slots (2g, 2g+1) = hi, lo of |scale| * sum q_g;
   // in lane group 3, slots (0, 1) = hi, lo of minus the running maximum
   h8 qsum_b[NR];
   int row_i[NR];
-#pragma unroll
-  for (int n = 0; n < NR; ++n) {
-    const int r = r0 + kRowsPerWave * wave + 16 * n + l16;
-    const int i = r / gq, hh = r % gq;
-    row_i[n] = i;
-    float gsum[NG];
-#pragma unroll
-    for (int g = 0; g < NG; ++g) gsum[g] = 0.0f;
-#pragma unroll
-    for (int s = 0; s < KSTEPS; ++s) {
-      h8 v;
-      if (i < T) {
-        const uint4 u = *reinterpret_cast<const uint4*>(
-            q + ((size_t)i * Hq + kv * gq + hh) * D + 32 * s + 8 * q4);
-        const uint32_t w[4] = {u.x, u.y, u.z, u.w};
-        _Float16 e8[8];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          e8[2 * e] = as_h2(w[e]).x;
-          e8[2 * e + 1] = as_h2(w[e]).y;
-        }
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-          v[e] = e8[kperm8(e)] * qsgn;
-          gsum[(32 * s) / G] += (float)v[e];
-        }
-      } else {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = (_Float16)0.0f;
-      }
-      qb[n][s] = v;
-    }
-    // complete the group sums over the 4 lanes of this row
-#pragma unroll
-    for (int g = 0; g < NG; ++g) {
-      gsum[g] += __shfl_xor(gsum[g], 16);
-      gsum[g] += __shfl_xor(gsum[g], 32);
-    }
-    h8 bq;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) bq[e] = (_Float16)0.0f;
-#pragma unroll
-    for (int g = 0; g < NG; ++g) {
-      if ((g >> 2) == q4) {
-        const float gs = gsum[g] * cabs;
-        const _Float16 hi = (_Float16)gs;
-        bq[2 * (g & 3)] = hi;
-        bq[2 * (g & 3) + 1] = (_Float16)(gs - (float)hi);
-      }
-    }
-    qsum_b[n] = bq;
-  }
-
   f32x4 acc_o[DT][NR];
   // m_run: the running maximum of |scale| * score; m_off: what the bias
   // product subtracts from the scores (m_run, or 0 before the first score
@@ -250,20 +263,7 @@ __global__ __launch_bounds__(64 * kWaves) void prefill_kernel(
   // m_run in every row of the wave (wave-uniform)
   float m_run[NR], l_run[NR], m_off[NR];
   bool folded = false;
-#pragma unroll
-  for (int n = 0; n < NR; ++n) {
-    m_run[n] = kMinit;
-    m_off[n] = 0.0f;
-    l_run[n] = 0.0f;
-#pragma unroll
-    for (int t = 0; t < DT; ++t) acc_o[t][n] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-  }
-
-  const int i_min = r0 / gq;
-  const int i_max = min(T - 1, (r0 + kRows - 1) / gq);
-  const int n_pre = (prefix_len + KT - 1) / KT;
-  const int n_chk = i_max / KT + 1;
-  const int n_tiles = n_pre + n_chk;
+  int i_min = 0;  // the row block's first position
 
   // ---- prefix tiles: codes and (scale, bias) words of tile j, one 16-byte
   // code chunk (and its one or two meta words) per thread and round.  K
@@ -408,6 +408,62 @@ __global__ __launch_bounds__(64 * kWaves) void prefill_kernel(
             *reinterpret_cast<uint32_t*>(&sV[b][d0 + 1][col]) =
                 as_u32(as_h2(__builtin_amdgcn_perm(wb[e], wa[e], 0x07060302u)) * half);
           }
+        }
+      }
+    }
+  };
+  // the same in two steps, for rows fetched a tile ahead (without a prefix):
+  // 32 dims of one key (K) or 16 dims of a key pair (V) per thread ...
+  auto load_chunk = [&](int j, uint4 (&u)[4]) {
+    if (tid < KCH) {
+      const int kk = j * KT + tid / QPK;
+      const uint4* src = reinterpret_cast<const uint4*>(k_chunk + ((size_t)kk * Hkv + kv) * D + 32 * (tid % QPK));
+#pragma unroll
+      for (int m = 0; m < 4; ++m) u[m] = (kk < T) ? src[m] : make_uint4(0, 0, 0, 0);
+    } else if (tid < KCH + VCH) {
+      const int cv = tid - KCH, kk = j * KT + 2 * (cv % (KT / 2)), u16 = cv / (KT / 2);
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {  // two chunks of the even key, two of the odd one
+        const int k = kk + (m >> 1);
+        const uint4* src = reinterpret_cast<const uint4*>(v_chunk + ((size_t)k * Hkv + kv) * D + 16 * u16);
+        u[m] = (k < T) ? src[m & 1] : make_uint4(0, 0, 0, 0);
+      }
+    }
+  };
+  // ... into buffer b
+  auto store_chunk = [&](const uint4 (&u)[4], int b) {
+    if (tid < KCH) {
+      const int key = tid / QPK, qd = tid % QPK;
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        // dims (0,1) (2,3) (4,5) (6,7) -> storage order (0,4) (1,5) (2,6) (3,7)
+        uint4 o;
+        o.x = __builtin_amdgcn_perm(u[m].z, u[m].x, 0x05040100u);
+        o.y = __builtin_amdgcn_perm(u[m].z, u[m].x, 0x07060302u);
+        o.z = __builtin_amdgcn_perm(u[m].w, u[m].y, 0x05040100u);
+        o.w = __builtin_amdgcn_perm(u[m].w, u[m].y, 0x07060302u);
+        *reinterpret_cast<uint4*>(&sK[b][key][32 * qd + 8 * m]) = o;
+      }
+      if ((32 * qd) % G == 0) {
+        const int g = (32 * qd) / G;
+        sKm[b][g][key] = cabs;  // scale 1, bias 0
+        sKb[b][key][g >> 2][g & 3] = 0u;
+      }
+    } else if (tid < KCH + VCH) {
+      const int cv = tid - KCH, pair = cv % (KT / 2), u16 = cv / (KT / 2);
+      const int col = vperm(2 * pair);
+#pragma unroll
+      for (int hv = 0; hv < 2; ++hv) {
+        const uint32_t wa[4] = {u[hv].x, u[hv].y, u[hv].z, u[hv].w};
+        const uint32_t wb[4] = {u[2 + hv].x, u[2 + hv].y, u[2 + hv].z, u[2 + hv].w};
+        const h2 half = {(_Float16)0.5f, (_Float16)0.5f};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int d0 = 16 * u16 + 8 * hv + 2 * e;
+          *reinterpret_cast<uint32_t*>(&sV[b][d0][col]) =
+              as_u32(as_h2(__builtin_amdgcn_perm(wb[e], wa[e], 0x05040100u)) * half);
+          *reinterpret_cast<uint32_t*>(&sV[b][d0 + 1][col]) =
+              as_u32(as_h2(__builtin_amdgcn_perm(wb[e], wa[e], 0x07060302u)) * half);
         }
       }
     }
@@ -575,7 +631,7 @@ __global__ __launch_bounds__(64 * kWaves) void prefill_kernel(
 #pragma unroll
         for (int n = 0; n < NR; ++n) acc_o[t][n] = mfma(a, pb[n][k], acc_o[t][n]);
       }
-    if (!chunk_tile) {  // the low parts of reconstructed values (block-uniform)
+    if (PRE && !chunk_tile) {  // the low parts of reconstructed values (block-uniform)
 #pragma unroll
       for (int t = 0; t < DT; ++t)
 #pragma unroll
@@ -595,80 +651,406 @@ __global__ __launch_bounds__(64 * kWaves) void prefill_kernel(
     (&sKb[0][0][0][0])[i] = (i & 15) == 12 ? 0x3C003C00u : 0u;  // (1, 1) in slots (0, 1) of lane group 3
   __syncthreads();
 
-  // ---- tiles 0 .. n_pre - 1 (prefix), then the chunk's; double-buffered:
-  // tile j + 1 is reconstructed and tile j + 2's codes are fetched while
-  // tile j is computed; one barrier per tile.  Waves w and w + 4 share a
-  // SIMD; the first half (the K chunks: the lighter reconstruction) does
-  // its part before the tile's products and the second half (the V chunks)
-  // after them, so that on each SIMD one wave's vector work meets the
-  // other's matrix products (measured 1.5 % faster than the other order).
-  int page_pf = -1;     // page of the tile in the prefetch registers
-  int page_buf[2] = {0, 0};
-  if (n_pre > 0) {
-    page_pf = tile_page(0);
-    prefetch(0, page_pf);
-    dequant(0, page_pf, 0);
-    page_buf[0] = page_pf;
-    if (n_pre > 1) {
-      page_pf = tile_page(1);
-      prefetch(1, page_pf);
-    }
-  } else {
-    stage_chunk(0, 0);
-  }
-  __syncthreads();
   const bool early = wave < kWaves / 2;  // wave-uniform
-  for (int j = 0; j < n_tiles; ++j) {
-    const int b = j & 1;
-    // this thread's part of tile j + 1 into buffer b ^ 1, and tile j + 2's codes
-    auto prep = [&]() {
-      if (j + 1 < n_tiles) {
-        if (j + 1 < n_pre) {
-          dequant(j + 1, page_pf, b ^ 1);
-          page_buf[b ^ 1] = page_pf;
+  for (;; ++rb, j0 = 0) {
+    const int r0 = rb * kRows;
+    i_min = r0 / gq;
+    const int n_tiles = n_pre + min(T - 1, (r0 + kRows - 1) / gq) / KT + 1;
+    const int j1 = ws ? min(n_tiles, j0 + left) : n_tiles;
+    // a wave whose rows all lie past the chunk's end only rebuilds the prefix
+    // tiles (for it, every page counts as invalid)
+    const bool idle = __builtin_amdgcn_readfirstlane((int)((r0 + kRowsPerWave * wave) / gq >= T)) != 0;
+    const unsigned np_on = idle ? 0u : (unsigned)NP;
+
+    // ---- Q^T operands, an empty softmax state
+  #pragma unroll
+    for (int n = 0; n < NR; ++n) {
+      const int r = r0 + kRowsPerWave * wave + 16 * n + l16;
+      const int i = r / gq, hh = r % gq;
+      row_i[n] = i;
+      float gsum[NG];
+  #pragma unroll
+      for (int g = 0; g < NG; ++g) gsum[g] = 0.0f;
+  #pragma unroll
+      for (int s = 0; s < KSTEPS; ++s) {
+        h8 v;
+        if (i < T) {
+          const uint4 u = *reinterpret_cast<const uint4*>(
+              q + ((size_t)i * Hq + kv * gq + hh) * D + 32 * s + 8 * q4);
+          const uint32_t w[4] = {u.x, u.y, u.z, u.w};
+          _Float16 e8[8];
+  #pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            e8[2 * e] = as_h2(w[e]).x;
+            e8[2 * e + 1] = as_h2(w[e]).y;
+          }
+  #pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            v[e] = e8[kperm8(e)] * qsgn;
+            gsum[(32 * s) / G] += (float)v[e];
+          }
         } else {
-          stage_chunk(j + 1 - n_pre, b ^ 1);
-          page_buf[b ^ 1] = 0;
+  #pragma unroll
+          for (int e = 0; e < 8; ++e) v[e] = (_Float16)0.0f;
+        }
+        qb[n][s] = v;
+      }
+      // complete the group sums over the 4 lanes of this row
+  #pragma unroll
+      for (int g = 0; g < NG; ++g) {
+        gsum[g] += __shfl_xor(gsum[g], 16);
+        gsum[g] += __shfl_xor(gsum[g], 32);
+      }
+      h8 bq;
+  #pragma unroll
+      for (int e = 0; e < 8; ++e) bq[e] = (_Float16)0.0f;
+  #pragma unroll
+      for (int g = 0; g < NG; ++g) {
+        if ((g >> 2) == q4) {
+          const float gs = gsum[g] * cabs;
+          const _Float16 hi = (_Float16)gs;
+          bq[2 * (g & 3)] = hi;
+          bq[2 * (g & 3) + 1] = (_Float16)(gs - (float)hi);
         }
       }
-      if (j + 2 < n_pre) {
-        page_pf = tile_page(j + 2);
-        prefetch(j + 2, page_pf);
-      }
-    };
-    const int page_cur = page_buf[b];
-    if (early) prep();
-    const bool chunk_tile = j >= n_pre;
-    if (chunk_tile)
-      compute(b, (j - n_pre) * KT, T, true);
-    else if ((unsigned)page_cur < (unsigned)NP)  // a tile on an invalid page is skipped
-      compute(b, j * KT, prefix_len, false);
-    if (!early) prep();
-    __syncthreads();
-  }
+      qsum_b[n] = bq;
+    }
 
-  // ---- O = acc / l, as fp16
+    folded = false;
+  #pragma unroll
+    for (int n = 0; n < NR; ++n) {
+      m_run[n] = kMinit;
+      m_off[n] = 0.0f;
+      l_run[n] = 0.0f;
+  #pragma unroll
+      for (int t = 0; t < DT; ++t) acc_o[t][n] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    }
+
+
+    // ---- tiles j0 .. j1 - 1 (prefix tiles 0 .. n_pre - 1, then the chunk's); double-buffered:
+    // tile j + 1 is reconstructed and tile j + 2's codes are fetched while
+    // tile j is computed; one barrier per tile.  Waves w and w + 4 share a
+    // SIMD; the first half (the K chunks: the lighter reconstruction) does
+    // its part before the tile's products and the second half (the V chunks)
+    // after them, so that on each SIMD one wave's vector work meets the
+    // other's matrix products (measured 1.5 % faster than the other order).
+    int page_pf = -1;     // page of the tile in the prefetch registers
+    int page_buf[2] = {0, 0};
+    uint4 cr[4];  // (without a prefix) the chunk rows of the tile fetched ahead
+    if constexpr (!PRE) {
+      load_chunk(j0, cr);
+      store_chunk(cr, j0 & 1);
+      if (j0 + 1 < j1) load_chunk(j0 + 1, cr);
+    } else if (j0 < n_pre) {
+      page_pf = tile_page(j0);
+      prefetch(j0, page_pf);
+      dequant(j0, page_pf, j0 & 1);
+      page_buf[j0 & 1] = page_pf;
+      if (j0 + 1 < min(n_pre, j1)) {
+        page_pf = tile_page(j0 + 1);
+        prefetch(j0 + 1, page_pf);
+      }
+    } else {
+      stage_chunk(j0 - n_pre, j0 & 1);
+    }
+    __syncthreads();
+    for (int j = j0; j < j1; ++j) {
+      const int b = j & 1;
+      // this thread's part of tile j + 1 into buffer b ^ 1, and tile j + 2's codes
+      auto prep = [&]() {
+        if constexpr (!PRE) {
+          if (j + 1 < j1) store_chunk(cr, b ^ 1);
+          if (j + 2 < j1) load_chunk(j + 2, cr);
+          return;
+        }
+        if (j + 1 < j1) {
+          if (j + 1 < n_pre) {
+            dequant(j + 1, page_pf, b ^ 1);
+            page_buf[b ^ 1] = page_pf;
+          } else {
+            stage_chunk(j + 1 - n_pre, b ^ 1);
+            page_buf[b ^ 1] = 0;
+          }
+        }
+        if (j + 2 < min(n_pre, j1)) {
+          page_pf = tile_page(j + 2);
+          prefetch(j + 2, page_pf);
+        }
+      };
+      const int page_cur = page_buf[b];
+      if (early) prep();
+      const bool chunk_tile = !PRE || j >= n_pre;
+      if (chunk_tile)
+        compute(b, (j - n_pre) * KT, T, true);
+      else if ((unsigned)page_cur < np_on)  // a tile on an invalid page is skipped
+        compute(b, j * KT, prefix_len, false);
+      if (!early) prep();
+      __syncthreads();
+    }
+
+    // ---- a part of the row block's tiles: the unnormalized state, as it lies
+    // in the registers, into one of the block's two slots (a share has at
+    // most one part that ends its row block and one that begins it)
+    if (j1 - j0 < n_tiles) {
+      float* rec = ws + (size_t)(2 * blockIdx.x + (j0 == 0)) * part_floats<D>() +
+                   wave * (part_floats<D>() / kWaves);
+      if (!idle) {
+#pragma unroll
+        for (int t = 0; t < DT; ++t)
+#pragma unroll
+          for (int n = 0; n < NR; ++n)
+            reinterpret_cast<f32x4*>(rec)[(t * NR + n) * 64 + lane] = acc_o[t][n];
+#pragma unroll
+        for (int n = 0; n < NR; ++n)
+          reinterpret_cast<float2*>(rec + DT * NR * 256)[n * 64 + lane] = make_float2(m_run[n], l_run[n]);
+      }
+    } else {
+      // ---- O = acc / l, as fp16
+    #pragma unroll
+      for (int n = 0; n < NR; ++n) {
+        const int r = r0 + kRowsPerWave * wave + 16 * n + l16;
+        const int i = r / gq, hh = r % gq;
+        // the row's sum: the four lanes of a query column hold disjoint keys
+        float l = l_run[n] + __shfl_xor(l_run[n], 16);
+        l += __shfl_xor(l, 32);
+        if (i >= T) continue;
+        const float inv = (l > 0.0f) ? 2.0f / l : 0.0f;  // (the value tiles hold V / 2)
+        __half* dst = out + ((size_t)i * Hq + kv * gq + hh) * D;
+    #pragma unroll
+        for (int t = 0; t < DT; ++t) {
+          const int d0 = 16 * t + 4 * q4;
+          store_o4(dst + d0, acc_o[t][n], inv);
+        }
+      }
+    }
+    if ((left -= j1 - j0) <= 0) break;
+  }
+}
+
+// Combine of the row blocks whose tiles were split over several blocks: the
+// log-sum-exp merge of their parts, in the registers' layout of the parts.
+// Block = (row block and KV head, wave of the row block, TW x TT of its D / 16
+// dim tiles); of its SW x TW waves each takes every SW-th part of TT dim tiles,
+// and the SW sums meet in LDS.  Latency-bound: the parts (at most two per block of the prefill
+// grid) come from the caches they were just written to, so the rule for SW
+// (launch_t) keeps a wave's chain of parts short, and few parts get few waves.
+template <int D, int SW, int TW, int TT>
+__global__ __launch_bounds__(64 * SW * TW) void prefill_combine_kernel(
+    const float* __restrict__ ws, __half* __restrict__ out, int T, int Hq, int Hkv, int prefix_len,
+    int n_blk, int head_tiles) {
+  constexpr int NR = row_tiles<D>();
+  constexpr int kRows = 16 * NR * kWaves;
+  constexpr int DT = D / 16;
+  constexpr int KT = keys_per_tile<D>();
+  static_assert(DT % (TW * TT) == 0, "whole tiles per block");
+  constexpr int NV = TT * NR;
+  __shared__ f32x4 s_acc[SW > 1 ? (SW - 1) * TW : 1][SW > 1 ? NV : 1][64];
+  __shared__ float2 s_ml[SW > 1 ? (SW - 1) * TW : 1][NR][64];
+  const int kv = blockIdx.x % Hkv, rb = blockIdx.x / Hkv;
+  const int rw = blockIdx.y;  // wave of the row block
+  const int gq = Hq / Hkv;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int r0 = rb * kRows + 16 * NR * rw;
+  if (r0 / gq >= T) return;  // no rows
+  const int n_pre = (prefix_len + KT - 1) / KT;
+  jfkv::RowBlockTiles rbt(kRows, T, gq, n_pre, KT);
+  int base = 0;
+  for (int i = 0; i < rb; ++i, rbt.next()) base += rbt.tiles();
+  const int end = base + rbt.tiles();
+  auto start = [&](int j) { return j * head_tiles / n_blk; };
+  auto owner = [&](int x) {  // the block whose share holds tile x
+    int j = x * n_blk / head_tiles;
+    while (start(j + 1) <= x) ++j;
+    while (start(j) > x) --j;
+    return j;
+  };
+  const int ja = owner(base), jb = owner(end - 1);
+  if (ja == jb) return;  // one block had them all and wrote the rows itself
+
+  const int sw = wave % SW, tw = wave / SW;
+  const int t0 = TT * (blockIdx.z * TW + tw);  // the wave's first dim tile
+  f32x4 acc[NV];
+  float m[NR], l[NR];
+#pragma unroll
+  for (int v = 0; v < NV; ++v) acc[v] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
   for (int n = 0; n < NR; ++n) {
-    const int r = r0 + kRowsPerWave * wave + 16 * n + l16;
-    const int i = r / gq, hh = r % gq;
-    // the row's sum: the four lanes of a query column hold disjoint keys
-    float l = l_run[n] + __shfl_xor(l_run[n], 16);
-    l += __shfl_xor(l, 32);
-    if (i >= T) continue;
-    const float inv = (l > 0.0f) ? 2.0f / l : 0.0f;  // (the value tiles hold V / 2)
-    __half* dst = out + ((size_t)i * Hq + kv * gq + hh) * D;
+    m[n] = kMinit;
+    l[n] = 0.0f;
+  }
+  auto fold = [&](int n, float2 ml, const f32x4* ao) {
+    const float M = fmaxf(m[n], ml.x);
+    const float fa = __builtin_amdgcn_exp2f(m[n] - M), fb = __builtin_amdgcn_exp2f(ml.x - M);
+    m[n] = M;
+    l[n] = l[n] * fa + ml.y * fb;
 #pragma unroll
-    for (int t = 0; t < DT; ++t) {
-      const int d0 = 16 * t + 4 * q4;
-      const __half2 a = __floats2half2_rn(acc_o[t][n][0] * inv, acc_o[t][n][1] * inv);
-      const __half2 c = __floats2half2_rn(acc_o[t][n][2] * inv, acc_o[t][n][3] * inv);
-      uint2 v;
-      v.x = __builtin_bit_cast(uint32_t, a);
-      v.y = __builtin_bit_cast(uint32_t, c);
-      *reinterpret_cast<uint2*>(dst + d0) = v;
+    for (int t = 0; t < TT; ++t) acc[t * NR + n] = acc[t * NR + n] * fa + ao[t * NR + n] * fb;
+  };
+#pragma unroll 2
+  for (int j = ja + sw; j <= jb; j += SW) {
+    const float* rec = ws + (size_t)(2 * (j * Hkv + kv) + (start(j) <= base)) * part_floats<D>() +
+                       rw * (part_floats<D>() / kWaves);
+    f32x4 ao[NV];
+    float2 ml[NR];
+#pragma unroll
+    for (int v = 0; v < NV; ++v)
+      ao[v] = reinterpret_cast<const f32x4*>(rec)[(t0 * NR + v) * 64 + lane];
+#pragma unroll
+    for (int n = 0; n < NR; ++n)
+      ml[n] = reinterpret_cast<const float2*>(rec + DT * NR * 256)[n * 64 + lane];
+#pragma unroll
+    for (int n = 0; n < NR; ++n) fold(n, ml[n], ao);
+  }
+  if constexpr (SW > 1) {
+    if (sw > 0) {
+      const int slot = (sw - 1) * TW + tw;
+#pragma unroll
+      for (int v = 0; v < NV; ++v) s_acc[slot][v][lane] = acc[v];
+#pragma unroll
+      for (int n = 0; n < NR; ++n) s_ml[slot][n][lane] = make_float2(m[n], l[n]);
+    }
+    __syncthreads();
+    if (sw > 0) return;
+    for (int w = 0; w < SW - 1; ++w) {
+      f32x4 ao[NV];
+#pragma unroll
+      for (int v = 0; v < NV; ++v) ao[v] = s_acc[w * TW + tw][v][lane];
+#pragma unroll
+      for (int n = 0; n < NR; ++n) fold(n, s_ml[w * TW + tw][n][lane], ao);
     }
   }
+#pragma unroll
+  for (int n = 0; n < NR; ++n) {
+    const int r = r0 + 16 * n + (lane & 15);
+    const int i = r / gq, hh = r % gq;
+    float ls = l[n] + __shfl_xor(l[n], 16);
+    ls += __shfl_xor(ls, 32);
+    if (i >= T) continue;
+    const float inv = (ls > 0.0f) ? 2.0f / ls : 0.0f;
+    __half* dst = out + ((size_t)i * Hq + kv * gq + hh) * D;
+#pragma unroll
+    for (int t = 0; t < TT; ++t) store_o4(dst + 16 * (t0 + t) + 4 * (lane >> 4), acc[t * NR + n], inv);
+  }
+}
+
+// How a call's work is laid over the chip: n_blk blocks per KV head share the
+// head's `tiles` key tiles (over all its row blocks) evenly, or n_blk = 0: one
+// block per row block.  A block fills a CU, so row blocks that do not fill the
+// chip, or leave its last turn nearly empty, cost as much as if they did.  An
+// even share costs a query load, a pipeline fill and a state to store for each
+// row block that it touches (kPartCost tiles) and the combine's launch and
+// reads (kCombineCost tiles), in tiles of about 3.3 us at head_dim 128, 2.1 us
+// at 64 and 256 (fitted to both layouts at 50 shapes of 20..2,048 rows over
+// 0..20,000 positions); a chunk without a prefix has tiles of 2.5 us, so there
+// both count twice.  Measured, split against one block per row block:
+// 256 rows over 196,608 (24/4 heads, 256) 2.50 against 13.1 ms; 1,000 over
+// 7,000 (32/8, 128) 218 against 392 us; 100 over 20,000 (4/1, 128) 37 against
+// 1,010 us; and where the rule keeps row blocks whole: 2,048 over none (32/8,
+// 128) 100 against 81 us, 1,000 over none 47 against 44 us.
+struct PrefillPlan {
+  int64_t n_rb = 0, tiles = 0;
+  int n_blk = 0;
+};
+template <int D>
+constexpr int64_t kPartCost = D == 128 ? 1 : D == 64 ? 2 : 5;
+template <int D>
+constexpr int64_t kCombineCost = D == 128 ? 3 : D == 64 ? 5 : 8;
+constexpr int64_t kMinShare = 4;   // tiles per block of a split call, at least
+constexpr int64_t kMaxTurns = 16;  // row blocks per CU above which the last turn hardly counts
+
+template <int D>
+PrefillPlan plan_t(const jf_kv_layout& L, int32_t T, int32_t Hq, int32_t prefix_len) {
+  constexpr int kRows = 16 * row_tiles<D>() * kWaves;
+  constexpr int KT = keys_per_tile<D>();
+  PrefillPlan p;
+  const int gq = Hq / L.num_kv_heads;
+  const int n_pre = (prefix_len + KT - 1) / KT;
+  p.n_rb = ((int64_t)T * gq + kRows - 1) / kRows;
+  const int64_t per_head = std::max(1, jfkv::num_cus() / L.num_kv_heads);
+  if (p.n_rb > kMaxTurns * per_head) return p;
+  int64_t whole = 0;  // tiles of the longest chain of row blocks on one CU
+  jfkv::RowBlockTiles rbt(kRows, T, gq, n_pre, KT);
+  for (int64_t rb = 0; rb < p.n_rb; ++rb, rbt.next()) {
+    p.tiles += rbt.tiles();
+    if (rb % per_head == per_head - 1 || rb == p.n_rb - 1) whole += rbt.tiles();
+  }
+  const int64_t n_blk = std::min(per_head, std::max<int64_t>(1, p.tiles / kMinShare));
+  const int64_t share = (p.tiles + n_blk - 1) / n_blk;
+  // row blocks that a share touches: most where they are shortest, at the start
+  int64_t touched = 1, at = 0;
+  rbt = jfkv::RowBlockTiles(kRows, T, gq, n_pre, KT);
+  for (; touched <= p.n_rb && (at += rbt.tiles()) < share; rbt.next()) ++touched;
+  const int64_t cost = (kPartCost<D> * (touched + 1) + kCombineCost<D>) * (n_pre ? 1 : 2);
+  if (n_blk > 1 && share + cost < whole &&
+      (n_blk + 1) * p.tiles <= INT32_MAX)  // (the kernels' products of shares and tiles)
+    p.n_blk = (int)n_blk;
+  return p;
+}
+
+PrefillPlan plan(const jf_kv_layout& L, int32_t T, int32_t Hq, int32_t prefix_len) {
+  return L.head_dim == 64    ? plan_t<64>(L, T, Hq, prefix_len)
+         : L.head_dim == 128 ? plan_t<128>(L, T, Hq, prefix_len)
+                             : plan_t<256>(L, T, Hq, prefix_len);
+}
+
+size_t plan_bytes(const jf_kv_layout& L, const PrefillPlan& p) {
+  const size_t part = L.head_dim == 64 ? part_floats<64>() : L.head_dim == 128 ? part_floats<128>() : part_floats<256>();
+  return 2 * (size_t)p.n_blk * L.num_kv_heads * part * sizeof(float);
+}
+
+template <int D, int G, bool PRE>
+hipError_t launch_t(const jf_kv_layout& L, const jf_kv_pool_ptrs& pool, const void* q,
+                    const void* k_chunk, const void* v_chunk, int32_t T, int32_t Hq,
+                    const int32_t* block_table, int32_t prefix_len, float softmax_scale, float* ws,
+                    const PrefillPlan& p, void* out, hipStream_t stream) {
+  const int64_t blocks = (ws ? p.n_blk : p.n_rb) * L.num_kv_heads;
+  hipLaunchKernelGGL((prefill_kernel<D, G, PRE>), dim3((uint32_t)blocks), dim3(64 * kWaves), 0, stream,
+                     static_cast<const uint8_t*>(pool.k_codes),
+                     static_cast<const uint32_t*>(pool.k_meta),
+                     static_cast<const uint8_t*>(pool.v_codes),
+                     static_cast<const uint32_t*>(pool.v_meta), static_cast<const __half*>(q),
+                     static_cast<const __half*>(k_chunk), static_cast<const __half*>(v_chunk),
+                     block_table, static_cast<__half*>(out), ws, T, Hq, L.num_kv_heads, L.page_size,
+                     L.num_pages, prefix_len, softmax_scale * kLog2e, p.n_blk, (int)p.tiles);
+  hipError_t e = hipGetLastError();
+  if (!ws || e != hipSuccess) return e;
+  const int64_t parts = p.n_blk / p.n_rb + 2;  // of a row block, about
+  auto combine = [&](auto kern, int waves, int tiles) {
+    dim3 grid((uint32_t)(p.n_rb * L.num_kv_heads), kWaves, D / 16 / tiles);
+    hipLaunchKernelGGL(kern, grid, dim3(64 * waves), 0, stream, ws, static_cast<__half*>(out), T,
+                       Hq, L.num_kv_heads, prefix_len, p.n_blk, (int)p.tiles);
+  };
+  constexpr int DT = D / 16;
+  if (parts <= 4)
+    combine(prefill_combine_kernel<D, 1, 4, DT / 4>, 4, DT);
+  else if (parts <= 16)
+    combine(prefill_combine_kernel<D, 4, 2, DT / 4>, 8, DT / 2);
+  else
+    combine(prefill_combine_kernel<D, 8, 1, 1>, 8, 1);
+  return hipGetLastError();
+}
+
+hipError_t dispatch(const jf_kv_layout& L, const jf_kv_pool_ptrs& pool, const void* q,
+                    const void* k_chunk, const void* v_chunk, int32_t T, int32_t Hq,
+                    const int32_t* block_table, int32_t prefix_len, float softmax_scale, float* ws,
+                    const PrefillPlan& p, void* out, hipStream_t stream) {
+#define JF_PREFILL_CASE(D_, G_)                                                                  \
+  if (L.head_dim == D_ && (prefix_len ? L.group_size == G_ : G_ == 32))                          \
+    return prefix_len ? launch_t<D_, G_, true>(JF_PREFILL_ARGS)                                  \
+                      : launch_t<D_, (D_ < 128 ? D_ : 128), false>(JF_PREFILL_ARGS);
+#define JF_PREFILL_ARGS                                                                          \
+  L, pool, q, k_chunk, v_chunk, T, Hq, block_table, prefix_len, softmax_scale, ws, p, out, stream
+  JF_PREFILL_CASE(64, 32)
+  JF_PREFILL_CASE(64, 64)
+  JF_PREFILL_CASE(128, 32)
+  JF_PREFILL_CASE(128, 64)
+  JF_PREFILL_CASE(128, 128)
+  JF_PREFILL_CASE(256, 32)
+  JF_PREFILL_CASE(256, 64)
+  JF_PREFILL_CASE(256, 128)
+#undef JF_PREFILL_CASE
+#undef JF_PREFILL_ARGS
+  return hipErrorInvalidValue;
 }
 
 }  // namespace
@@ -680,33 +1062,40 @@ hipError_t launch_prefill(const jf_kv_layout& L, const jf_kv_pool_ptrs& pool, co
                           const int32_t* block_table, int32_t max_pages, int32_t prefix_len,
                           float softmax_scale, void* out, hipStream_t stream) {
   (void)max_pages;  // validated on the host: prefix_len <= max_pages * page_size
-  const int gq = Hq / L.num_kv_heads;
-  const int64_t rows = (int64_t)T * gq;
-#define JF_PREFILL_CASE(D_, G_)                                                                 \
-  if (L.head_dim == D_ && L.group_size == G_) {                                                 \
-    constexpr int kRowsB = 16 * row_tiles<D_>() * kWaves;                                      \
-    const int64_t n_rb = (rows + kRowsB - 1) / kRowsB;                                          \
-    dim3 grid((uint32_t)(n_rb * L.num_kv_heads));                                               \
-    hipLaunchKernelGGL((prefill_kernel<D_, G_>), grid, dim3(64 * kWaves), 0, stream,    \
-                       static_cast<const uint8_t*>(pool.k_codes),                               \
-                       static_cast<const uint32_t*>(pool.k_meta),                               \
-                       static_cast<const uint8_t*>(pool.v_codes),                               \
-                       static_cast<const uint32_t*>(pool.v_meta), static_cast<const __half*>(q),\
-                       static_cast<const __half*>(k_chunk), static_cast<const __half*>(v_chunk),\
-                       block_table, static_cast<__half*>(out), T, Hq, L.num_kv_heads,           \
-                       L.page_size, L.num_pages, prefix_len, softmax_scale * kLog2e);           \
-    return hipGetLastError();                                                                   \
-  }
-  JF_PREFILL_CASE(64, 32)
-  JF_PREFILL_CASE(64, 64)
-  JF_PREFILL_CASE(128, 32)
-  JF_PREFILL_CASE(128, 64)
-  JF_PREFILL_CASE(128, 128)
-  JF_PREFILL_CASE(256, 32)
-  JF_PREFILL_CASE(256, 64)
-  JF_PREFILL_CASE(256, 128)
-#undef JF_PREFILL_CASE
-  return hipErrorInvalidValue;
+  PrefillPlan p;
+  const int rows = 16 * kWaves * (L.head_dim > 128 ? row_tiles<256>() : row_tiles<128>());
+  p.n_rb = ((int64_t)T * (Hq / L.num_kv_heads) + rows - 1) / rows;
+  return dispatch(L, pool, q, k_chunk, v_chunk, T, Hq, block_table, prefix_len, softmax_scale,
+                  nullptr, p, out, stream);
 }
 
 }  // namespace jfkv
+
+jf_status jf_prefill_workspace_bytes(const jf_kv_layout* layout, int32_t T, int32_t num_q_heads,
+                                     int32_t prefix_len, size_t* bytes) {
+  jf_status st = jfkv::check_prefill_shape(layout, T, num_q_heads, prefix_len);
+  if (st) return st;
+  if (!bytes) return jfkv::status_invalid("NULL output pointer");
+  *bytes = T ? plan_bytes(*layout, plan(*layout, T, num_q_heads, prefix_len)) : 0;
+  return JF_OK;
+}
+
+jf_status jf_prefill_attn_q4_ws(const jf_kv_layout* layout, const jf_kv_pool_ptrs* pool,
+                                const void* q, const void* k_chunk, const void* v_chunk,
+                                int32_t T, int32_t num_q_heads, const int32_t* block_table,
+                                int32_t max_pages, int32_t prefix_len, float softmax_scale,
+                                void* workspace, size_t workspace_bytes, void* out,
+                                hipStream_t stream) {
+  jf_status st = jfkv::check_prefill(layout, pool, q, k_chunk, v_chunk, T, num_q_heads,
+                                     block_table, max_pages, prefix_len, softmax_scale, out);
+  if (st || T == 0) return st;
+  const PrefillPlan p = plan(*layout, T, num_q_heads, prefix_len);
+  if (p.n_blk && (!workspace || ((uintptr_t)workspace & 15) || workspace_bytes < plan_bytes(*layout, p)))
+    return jfkv::status_invalid("workspace NULL, not 16-byte aligned or smaller than "
+                                "jf_prefill_workspace_bytes()");
+  return jfkv::status_of(dispatch(*layout, *pool, q, k_chunk, v_chunk, T, num_q_heads, block_table,
+                                  prefix_len, softmax_scale,
+                                  p.n_blk ? static_cast<float*>(workspace) : nullptr, p, out,
+                                  stream),
+                         "prefill launch");
+}

@@ -29,7 +29,7 @@ EXPORTS = [
     "jf_page_table_stats", "jf_page_table_info",
     "jf_kv_quantize_append", "jf_decode_workspace_bytes", "jf_decode_attn_q4",
     "jf_verify_attn_q4", "jf_decode_step_q4", "jf_decode_step_q4_static", "jf_prefill_attn_q4",
-    "jf_reconstruct_q4", "jf_tq4_pool_bytes", "jf_tq4_encode_append", "jf_tq4_decode_attn",
+    "jf_prefill_workspace_bytes", "jf_prefill_attn_q4_ws", "jf_reconstruct_q4", "jf_tq4_pool_bytes", "jf_tq4_encode_append", "jf_tq4_decode_attn",
     "jf_tq4_reconstruct", "jf_kv_page_bytes", "jf_kv_pack_pages", "jf_kv_unpack_pages",
     "jf_snapshot_save", "jf_snapshot_restore", "jf_calib_read_stream",
 ]
@@ -90,6 +90,9 @@ def _load():
         "jf_decode_step_q4_static": (st, [P, P, P, P, P, i32, i32, P, i32, P, ctypes.c_float,
                                           i32, P, P]),
         "jf_prefill_attn_q4": (st, [P, P, P, P, P, i32, i32, P, i32, i32, ctypes.c_float, P, P]),
+        "jf_prefill_workspace_bytes": (st, [P, i32, i32, i32, ctypes.POINTER(sz)]),
+        "jf_prefill_attn_q4_ws": (st, [P, P, P, P, P, i32, i32, P, i32, i32, ctypes.c_float, P, sz,
+                                       P, P]),
         "jf_reconstruct_q4": (st, [P, P, P, i32, i32, i32, i32, P, P, P]),
         "jf_tq4_reconstruct": (st, [P, P, P, P, P, P, P, P, P, i32, i32, i32, i32, P, P, P]),
         "jf_kv_page_bytes": (st, [P, ctypes.POINTER(sz)]),
@@ -408,16 +411,62 @@ def _check_prefill_args(pool: KVPool, q, k_chunk, v_chunk, block_table, out):
         raise ValueError("k_chunk/v_chunk must be [T][Hkv][head_dim]")
 
 
+def jf_prefill_workspace_bytes(lay: Layout, T: int, num_q_heads: int, prefix_len: int) -> int:
+    n = ctypes.c_size_t()
+    _check(lib.jf_prefill_workspace_bytes(ctypes.byref(lay), T, num_q_heads, prefix_len,
+                                          ctypes.byref(n)))
+    return n.value
+
+
+def _prefill_call(head, tail, nbytes: int, device, stream):
+    """One prefill launch: head and tail are the call's arguments around the
+    workspace.  The scratch of a split call comes from torch's caching
+    allocator on the call's own stream (so later work on that stream may reuse
+    it, and empty_cache() gives it back) and is held for the call only.  Without
+    it (none needed, none to be had, or a stream under capture, whose replays
+    would outlive it) the call runs unsplit."""
+    import torch
+    ws = None
+    if nbytes and device.index == torch.cuda.current_device():
+        if stream is not None and not isinstance(stream, torch.cuda.Stream):
+            stream = torch.cuda.ExternalStream(stream.cuda_stream)
+        with torch.cuda.stream(stream):  # (None: the current stream)
+            if not torch.cuda.is_current_stream_capturing():
+                try:
+                    ws = torch.empty(nbytes, dtype=torch.uint8, device=device)
+                except torch.OutOfMemoryError:
+                    pass
+    if ws is None:
+        _check(lib.jf_prefill_attn_q4(*head, *tail))
+    else:
+        _check(lib.jf_prefill_attn_q4_ws(*head, ws.data_ptr(), nbytes, *tail))
+
+
+def _prefill_args(pool: KVPool, q, k_chunk, v_chunk, block_table, prefix_len, softmax_scale, out,
+                  stream):
+    _check_prefill_args(pool, q, k_chunk, v_chunk, block_table, out)
+    lay, ptrs = pool.layout, pool.ptrs()
+    T, Hq, _ = q.shape
+    head = (ctypes.byref(lay), ctypes.byref(ptrs), _ptr(q), _ptr(k_chunk), _ptr(v_chunk), T, Hq,
+            _ptr(block_table), block_table.shape[-1], int(prefix_len), float(softmax_scale))
+    tail = (_ptr(out), _stream(stream))
+    nbytes = 0
+    if prefix_len + T > 256:  # (below, a split never pays: at most eight tiles per row block)
+        try:
+            nbytes = jf_prefill_workspace_bytes(lay, T, Hq, int(prefix_len))
+        except JfError:  # sizes the call itself refuses, with its own message
+            pass
+    return head, tail, nbytes, (lay, ptrs)
+
+
 def jf_prefill_attn_q4(pool: KVPool, q, k_chunk, v_chunk, block_table, prefix_len: int,
                        softmax_scale: float, out, stream=None):
-    _check_prefill_args(pool, q, k_chunk, v_chunk, block_table, out)
-    lay = pool.layout
-    T, Hq, d = q.shape
-    ptrs = pool.ptrs()
-    _check(lib.jf_prefill_attn_q4(ctypes.byref(lay), ctypes.byref(ptrs), _ptr(q), _ptr(k_chunk),
-                                  _ptr(v_chunk), T, Hq, _ptr(block_table), block_table.shape[-1],
-                                  int(prefix_len), float(softmax_scale), _ptr(out),
-                                  _stream(stream)))
+    head, tail, nbytes, _ = _prefill_args(pool, q, k_chunk, v_chunk, block_table, prefix_len,
+                                          softmax_scale, out, stream)
+    if nbytes:
+        _prefill_call(head, tail, nbytes, q.device, stream)
+    else:
+        _check(lib.jf_prefill_attn_q4(*head, *tail))
 
 
 # ------------------------------------------------------------ pre-bound calls
@@ -487,16 +536,24 @@ def bind_verify(pool: KVPool, q, block_tables, seq_lens, softmax_scale, max_spli
                      (lay, ptrs, pool, q, block_tables, seq_lens, workspace, out))
 
 
+class BoundPrefill(BoundCall):
+    """A bound prefill; a split call's workspace is taken for each call."""
+
+    def __init__(self, head, tail, nbytes, device, stream, keep):
+        super().__init__(None, (head, tail, nbytes, device, stream), keep)
+
+    def __call__(self):
+        _prefill_call(*self._args)
+
+
 def bind_prefill(pool: KVPool, q, k_chunk, v_chunk, block_table, prefix_len, softmax_scale, out,
                  stream=None) -> BoundCall:
-    _check_prefill_args(pool, q, k_chunk, v_chunk, block_table, out)
-    lay, ptrs = pool.layout, pool.ptrs()
-    T, Hq, _ = q.shape
-    args = (ctypes.byref(lay), ctypes.byref(ptrs), _ptr(q), _ptr(k_chunk), _ptr(v_chunk), T, Hq,
-            _ptr(block_table), block_table.shape[-1], int(prefix_len), float(softmax_scale),
-            _ptr(out), _stream(stream))
-    return BoundCall(lib.jf_prefill_attn_q4, args,
-                     (lay, ptrs, pool, q, k_chunk, v_chunk, block_table, out))
+    import torch
+    stream = torch.cuda.current_stream() if stream is None else stream
+    head, tail, nbytes, own = _prefill_args(pool, q, k_chunk, v_chunk, block_table, prefix_len,
+                                            softmax_scale, out, stream)
+    return BoundPrefill(head, tail, nbytes, q.device, stream,
+                        (*own, pool, q, k_chunk, v_chunk, block_table, out))
 
 
 def jf_reconstruct_q4(pool: KVPool, block_table, n_pos: int, kv0: int, num_heads: int, k_out,

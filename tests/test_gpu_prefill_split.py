@@ -1,0 +1,87 @@
+"""GPU prefill with its key tiles shared evenly over the chip
+(jf_prefill_attn_q4_ws) against the CPU oracle and against the call that keeps
+row blocks whole (jf_prefill_attn_q4), at shapes whose shares end inside a row
+block, on its edge, and span several row blocks, with last tiles that are
+partial, waves without rows, and a page outside the pool.
+
+Both calls run the same products per tile; only the fp32 sums over tiles are
+taken in another order (and relative to another running maximum, so p is
+rounded to fp16 at another scale, at most 2^-11 relative each): they agree to
+the tolerance both hold against the oracle, 2e-3 + 2^-11 |o| elementwise and
+1e-3 in relative L2."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+from paper_2609_17475_amd import jfkv
+
+
+def test_prefill_workspace_bytes_and_validation():
+    lay = jfkv.layout(256, 8, 128, 64, 16)
+    # the state of a 256-row block: o, and m and l for each of a row's four lanes
+    part = 256 * (128 + 4 * 2) * 4
+    # a full chunk of whole turns without a prefix worth sharing needs none
+    assert jfkv.jf_prefill_workspace_bytes(lay, 0, 32, 0) == 0
+    assert jfkv.jf_prefill_workspace_bytes(lay, 64, 32, 0) == 0
+    # bounded by two states per compute unit, whatever the lengths
+    for T, p0 in ((20, 3000), (256, 200000), (1000, 7000), (2049, 65536)):
+        n = jfkv.jf_prefill_workspace_bytes(lay, T, 32, p0)
+        assert 0 < n <= 2 * 256 * part and n % part == 0
+    with pytest.raises(jfkv.JfError):
+        jfkv.jf_prefill_workspace_bytes(lay, 64, 30, 0)
+    ptrs = jfkv.PoolPtrs(1, 1, 1, 1)
+    call = jfkv.lib.jf_prefill_attn_q4_ws
+    for ws, n in ((None, 1 << 40), (16, 100), (8, 1 << 40)):
+        assert call(ctypes.byref(lay), ctypes.byref(ptrs), 1, 1, 1, 20, 32, 1, 16, 3000, 1.0, ws, n,
+                    1, None) == jfkv.JF_ERR_INVALID
+        assert b"workspace" in jfkv.lib.jf_last_error()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("P,hkv,hq,d,G,p0,T,scale,bad", [
+    (256, 1, 4, 128, 64, 5000, 37, 1.0, None),    # one row block, waves without rows
+    (64, 2, 8, 128, 32, 3001, 130, -0.7, None),   # three row blocks, partial last tiles
+    (256, 1, 8, 128, 128, 2048, 64, 1.0, 3),      # whole pages, one outside the pool
+    (64, 1, 2, 64, 64, 2111, 300, 1.0, None),
+    (256, 4, 24, 256, 64, 1500, 50, 1.0, None),   # 32-key tiles
+    (64, 1, 16, 256, 32, 900, 29, 1.3, 5),
+    (64, 1, 4, 128, 64, 0, 1700, 1.0, None),      # shares over several short row blocks
+])
+def test_split_prefill_matches_oracle_and_whole_row_blocks(P, hkv, hq, d, G, p0, T, scale, bad):
+    import oracle
+    from gpu_cases import build, check_tol, log
+    log("split prefill P=%d hkv=%d hq=%d d=%d G=%d p0=%d T=%d scale=%g bad=%s" % (
+        P, hkv, hq, d, G, p0, T, scale, bad))
+    case = build(P=P, hkv=hkv, d=d, G=G, hq=hq, lens=(p0 + T,), n_out=2, seed=p0 + T)
+    rng = np.random.default_rng(p0 * 5 + T)
+    kc = rng.standard_normal((T, hkv, d)).astype(np.float16)
+    vc = rng.standard_normal((T, hkv, d)).astype(np.float16)
+    q = (rng.standard_normal((T, hq, d)) / np.sqrt(d)).astype(np.float16)
+    table = np.ascontiguousarray(case.tables[0])
+    if bad is not None:
+        table[bad] = case.lay.num_pages + 7
+    nbytes = jfkv.jf_prefill_workspace_bytes(case.lay, T, hq, p0)
+    assert nbytes > 0
+    args = [torch.from_numpy(x).cuda() for x in (q, kc, vc, table)]
+    split = torch.full(q.shape, float("nan"), dtype=torch.float16, device="cuda")
+    whole = split.clone()
+    # the binding takes the workspace by itself; poison what it may be given
+    torch.full((nbytes,), 0xA5, dtype=torch.uint8, device="cuda")
+    jfkv.jf_prefill_attn_q4(case.gpu, *args, p0, scale, split)
+    bound = torch.full_like(split, float("nan"))
+    jfkv.bind_prefill(case.gpu, *args, p0, scale, bound)()
+    lay, ptrs = case.lay, case.gpu.ptrs()
+    jfkv._check(jfkv.lib.jf_prefill_attn_q4(
+        ctypes.byref(lay), ctypes.byref(ptrs), *(a.data_ptr() for a in args[:3]), T, hq,
+        args[3].data_ptr(), len(table), p0, scale, whole.data_ptr(),
+        torch.cuda.current_stream().cuda_stream))
+    torch.cuda.synchronize()
+    assert torch.equal(split, bound)
+    tol = dict(atol=2e-3, rel_elem=2.0 ** -11, rel_l2=1e-3)
+    check_tol(split.cpu().numpy(), whole.double().cpu().numpy(), what="split against whole", **tol)
+    if bad is not None:  # (the oracle takes no page outside the pool)
+        return
+    ref = oracle.prefill(case.host, q, kc, vc, table, p0, scale)
+    log("  max err %.3e rel L2 %.3e" % check_tol(split.cpu().numpy(), ref, what="split", **tol))
