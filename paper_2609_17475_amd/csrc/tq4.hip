@@ -5,14 +5,27 @@
 // u32 word and stored with the fp16 norm at the vector's page slot
 // (Appendix A, Table codec; Background, page table).
 //
-// One wave per vector at a time, eight vectors per wave (their loads issued
-// together).  Lane l holds elements 4l .. 4l + 3 (one 8-byte load: the 64
-// lanes read the vector's 512 bytes in one coalesced access).  The
-// Walsh-Hadamard transform takes the first two of its eight butterfly stages
-// inside each lane (element index bits 0 and 1) and the other six across
-// lanes (index bits 2..7 are lane bits 0..5), with one exchange per stage and
-// value (DPP, swizzle or lane permute: no LDS addresses).  The norm is a wave-wide sum of squares: IEEE addition commutes, so
-// every lane of the butterfly reduction ends with the same sum.
+// A wave transforms four vectors at a time, one per row of 16 lanes.  The lane
+// of chunk c (0..15) holds elements 8c .. 8c + 7 and 128 + 8c .. 128 + 8c + 7
+// (two 16-byte loads; 16 lanes read 256 contiguous bytes each time).  Of the
+// eight butterfly stages of the Walsh-Hadamard transform, those on element
+// index bits 0, 1, 2 and 7 stay in the lane and those on bits 3..6 (the bits of
+// c) exchange with another lane of the row.  Lane r of the row holds the chunk
+// c with r = c0 * 1 ^ c1 * 2 ^ c2 * 7 ^ c3 * 15, so that the four exchanges are
+// the lane permutations a DPP operand can make by itself (pairs swapped, quad
+// halves swapped, half row and row mirrored), and a stage is one instruction
+// per element: f = e + sg * partner(e) with sg = -1 in the lanes whose bit is
+// set, which there is minus the butterfly's output.  A pair of lanes differs
+// only in the bit of its own stage, so the signs left by earlier stages agree
+// in it and multiply to one sign per lane, which the final scaling takes out.
+// (One lane per four elements, 64 lanes per vector, needed six exchanges of
+// every element, four of them through the LDS unit.)  The additions and their
+// order are those of the textbook in-place transform, stage by stage.  The norm
+// is a wave-wide sum of squares: IEEE addition commutes, so every lane of the
+// butterfly reduction ends with the same sum.
+//
+// What bounds the kernels: vector issue, then HBM.  Per vector ~80 vector
+// instructions and 4 LDS reads (~146 and ~25 before this layout).
 //
 // Index of a coordinate: the number of midpoint thresholds between adjacent
 // centroids that it strictly exceeds (a coordinate on a threshold keeps the
@@ -22,17 +35,23 @@
 // bucket is lower lies below y and every one in a higher bucket above it;
 // an entry holds the count of thresholds in lower buckets and the one
 // threshold of its bucket (+inf if none), and the index is that count plus
-// one comparison.  If a codebook puts two thresholds in one bucket, the block
+// one comparison.  The table is held 32 times, copy k in the k-th pair of
+// banks, so that a wave's reads of random entries do not collide; the map is
+// computed in the mantissa of 2^15 + bucket (a fraction of 8 bits below the
+// bucket number), whose bits, masked, are the entry's byte address.  If a codebook puts two thresholds in one bucket, the block
 // uses a 4-step binary search over the midpoints instead.  Both give the
 // same index for every y.  y is the transformed vector times one correctly
 // rounded reciprocal of 16 rho.
 //
 // The destination of a row (request, logical position, page) is looked up
-// once per row: a wave's vectors are consecutive, Hkv of them per row.
+// with scalar loads where the four vectors are heads of one row (always, when
+// the head count is a multiple of four), otherwise per vector.
 // A vector of norm 0 has every coordinate 0.
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <algorithm>
 
 #include "jfkv.h"
 #include "jfkv_internal.h"
@@ -41,187 +60,265 @@ namespace {
 
 constexpr int kD = 256;          // head dimension of the format
 constexpr int kWavesPerBlock = 4;
-constexpr int kVecPerWave = 8;   // vectors per wave, their loads issued together
+constexpr int kBatch = 4;        // vectors of a wave at a time
 constexpr int kLevels = 16;
 constexpr int kBuckets = 64;     // index buckets (at most one threshold each)
+constexpr int kCopies = 32;      // of the bucket table: one per pair of LDS banks
 
-__device__ __forceinline__ float2 h2_to_f2(uint32_t u) {
-  return __half22float2(__builtin_bit_cast(__half2, u));
+typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+// Rows and operands are 8-byte aligned, by contract; global memory takes a
+// 16-byte access at any 4-byte address, and nothing else here relies on the
+// alignment of a u32x4 in memory.
+
+// The lane that differs in bit K of the chunk number (see above).
+template <int K>
+__device__ __forceinline__ float partner(float v) {
+  constexpr int kCtrl[4] = {0xB1, 0x4E, 0x141, 0x140};  // quad_perm 1,0,3,2; 2,3,0,1; half, row mirror
+  return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), kCtrl[K],
+                                                            0xF, 0xF, true));
 }
 
-// The value of lane ^ M (M = 1 .. 32) of the same wave: a DPP quad
-// permutation for M = 1, 2 (a VALU move), a bit-mask swizzle within each
-// 32-lane half for M = 4, 8, 16, a lane permute for M = 32.
-template <int M>
-__device__ __forceinline__ float xor_lane(float v) {
-  const int i = __builtin_bit_cast(int, v);
-  if constexpr (M == 1)
-    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(i, 0xB1, 0xF, 0xF, true));
-  else if constexpr (M == 2)
-    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(i, 0x4E, 0xF, 0xF, true));
-  else if constexpr (M < 32)
-    return __builtin_bit_cast(float, __builtin_amdgcn_ds_swizzle(i, (M << 10) | 0x1F));
-  else
-    return __shfl_xor(v, M, 64);
+// Chunk held by lane r of a row, and the signs of the four exchanges.
+struct RowLane {
+  int chunk;
+  float sg[4], sign;  // sign: their product
+  __device__ __forceinline__ explicit RowLane(int r) {
+    const int r0 = r & 1, r1 = (r >> 1) & 1, r2 = (r >> 2) & 1, r3 = r >> 3;
+    const int c[4] = {r0 ^ r2, r1 ^ r2, r2 ^ r3, r3};
+    chunk = c[0] + 2 * c[1] + 4 * c[2] + 8 * c[3];
+    sign = 1.0f;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      sg[k] = c[k] ? -1.0f : 1.0f;
+      sign *= sg[k];
+    }
+  }
+};
+
+// The four exchanging stages (element index bits 3..6): one instruction per
+// element and stage.  Written out, since the compiler makes each a move with
+// the permutation and an fma; a DPP operand may not be read within two wait
+// states of being written, which the s_nop (before the first stage) and the
+// sixteen instructions of a stage (between stages) provide.  Every lane of the
+// wave is active here.
+__device__ __forceinline__ void exchange_stages(float (&e)[2][8], const RowLane& rl) {
+#define JF_X(R, S, C) "v_fmac_f32_dpp %" #R ", %" #R ", %" #S " " C " row_mask:0xf bank_mask:0xf\n\t"
+#define JF_STAGE(S, C)                                                                          \
+  JF_X(0, S, C) JF_X(1, S, C) JF_X(2, S, C) JF_X(3, S, C) JF_X(4, S, C) JF_X(5, S, C)           \
+  JF_X(6, S, C) JF_X(7, S, C) JF_X(8, S, C) JF_X(9, S, C) JF_X(10, S, C) JF_X(11, S, C)         \
+  JF_X(12, S, C) JF_X(13, S, C) JF_X(14, S, C) JF_X(15, S, C)
+  asm("s_nop 1\n\t" JF_STAGE(16, "quad_perm:[1,0,3,2]") JF_STAGE(17, "quad_perm:[2,3,0,1]")
+      JF_STAGE(18, "row_half_mirror") JF_STAGE(19, "row_mirror")
+      : "+&v"(e[0][0]), "+&v"(e[0][1]), "+&v"(e[0][2]), "+&v"(e[0][3]), "+&v"(e[0][4]), "+&v"(e[0][5]),
+        "+&v"(e[0][6]), "+&v"(e[0][7]), "+&v"(e[1][0]), "+&v"(e[1][1]), "+&v"(e[1][2]), "+&v"(e[1][3]),
+        "+&v"(e[1][4]), "+&v"(e[1][5]), "+&v"(e[1][6]), "+&v"(e[1][7])
+      : "v"(rl.sg[0]), "v"(rl.sg[1]), "v"(rl.sg[2]), "v"(rl.sg[3]));
+#undef JF_STAGE
+#undef JF_X
 }
 
-// One cross-lane butterfly stage on lane bit log2(M): the lane with the bit
-// set takes partner - own, the other own + partner (an fma by +-1 is exact).
-template <int M>
-__device__ __forceinline__ void stage(float& e0, float& e1, float& e2, float& e3, int lane) {
-  const float sg = (lane & M) ? -1.0f : 1.0f;
-  const float p0 = xor_lane<M>(e0), p1 = xor_lane<M>(e1);
-  const float p2 = xor_lane<M>(e2), p3 = xor_lane<M>(e3);
-  e0 = fmaf(sg, e0, p0);
-  e1 = fmaf(sg, e1, p1);
-  e2 = fmaf(sg, e2, p2);
-  e3 = fmaf(sg, e3, p3);
+// Stages 1..7 of the transform (stage 0, on neighbouring elements, is the
+// caller's); leaves rl.sign times the result.
+__device__ __forceinline__ void fwht_from1(float (&e)[2][8], const RowLane& rl) {
+#pragma unroll
+  for (int m = 2; m <= 4; m *= 2)
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        if (!(i & m)) {
+          const float u = e[h][i], v = e[h][i + m];
+          e[h][i] = u + v;
+          e[h][i + m] = u - v;
+        }
+  exchange_stages(e, rl);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const float u = e[0][i], v = e[1][i];
+    e[0][i] = u + v;
+    e[1][i] = u - v;
+  }
 }
 
 __global__ __launch_bounds__(64 * kWavesPerBlock) void tq4_encode_kernel(
-    uint32_t* __restrict__ words, __half* __restrict__ norms, const uint2* __restrict__ x,
+    uint32_t* __restrict__ words, __half* __restrict__ norms, const u32x4* __restrict__ x,
     const float* __restrict__ signs, const float* __restrict__ centroids,
     const int32_t* __restrict__ cu_tok, const int32_t* __restrict__ start_pos,
     const int32_t* __restrict__ block_tables, int B, int max_pages, int Hkv, int P, int NP,
     int n_vec) {
   // thresholds for a 4-step binary search: entry 15 is +inf (never passed)
   __shared__ float thr[kLevels];
-  // bucket table: y falls in bucket b = clamp(floor(fma(y, bk_inv, bk_off)),
+  // bucket table: y falls in bucket b = clamp(floor(y * bk_inv + bk_off),
   // 0, kBuckets - 1), a monotone map, so every threshold in a lower bucket is
   // below y and every one in a higher bucket above it; entry b holds their
   // count (below) and the bucket's own threshold (+inf if none)
-  __shared__ float2 bucket[kBuckets];
+  __shared__ __attribute__((aligned(256 * kBuckets))) float2 bucket[kBuckets][kCopies];
   __shared__ int s_multi;  // a bucket holds two thresholds: binary search instead
-  if (threadIdx.x < kLevels)
-    thr[threadIdx.x] = threadIdx.x < kLevels - 1
-                           ? (centroids[threadIdx.x] + centroids[threadIdx.x + 1]) * 0.5f
-                           : INFINITY;
-  if (threadIdx.x == 0) s_multi = 0;
+  const int tid = threadIdx.x;
+  if (tid < kLevels)
+    thr[tid] = tid < kLevels - 1 ? (centroids[tid] + centroids[tid + 1]) * 0.5f : INFINITY;
+  if (tid == 0) s_multi = 0;
   __syncthreads();
   // buckets of width (t_14 - t_0) / (kBuckets - 2) from one width below t_0
   const float t_first = thr[0], t_last = thr[kLevels - 2];
   const float bk_inv = (float)(kBuckets - 2) / (t_last - t_first);
-  const float bk_off = 1.0f - t_first * bk_inv;
-  auto bucket_of = [&](float y) {  // (clamped before the conversion: no overflow)
-    return (int)__builtin_amdgcn_fmed3f(fmaf(y, bk_inv, bk_off), 0.0f, (float)(kBuckets - 1));
+  constexpr float kMagic = 32768.0f;  // 8 bits of fraction below the bucket number
+  constexpr uint32_t kMask = (kBuckets - 1) << 8;
+  const float bk_off = kMagic + 1.0f - t_first * bk_inv;
+  auto bucket_bits = [&](float y) {  // the bucket number in bits 8..13
+    return __builtin_bit_cast(uint32_t, __builtin_amdgcn_fmed3f(fmaf(y, bk_inv, bk_off), kMagic,
+                                                                kMagic + (kBuckets - 1)));
   };
-  if (threadIdx.x < kBuckets) {
+  for (int i = tid; i < kBuckets * 4; i += 64 * kWavesPerBlock) {
+    const uint32_t bk = i >> 2;
     int below = 0, inside = 0;
     float t_in = INFINITY;
     for (int k = 0; k < kLevels - 1; ++k) {
-      const int bt = bucket_of(thr[k]);
-      below += bt < (int)threadIdx.x;
-      if (bt == (int)threadIdx.x) {
+      const uint32_t bt = (bucket_bits(thr[k]) & kMask) >> 8;
+      below += bt < bk;
+      if (bt == bk) {
         ++inside;
         t_in = thr[k];
       }
     }
-    bucket[threadIdx.x] = make_float2(__builtin_bit_cast(float, below), t_in);
+    for (int k = 0; k < kCopies / 4; ++k)
+      bucket[bk][(i & 3) * (kCopies / 4) + k] = make_float2(__builtin_bit_cast(float, below), t_in);
     if (inside > 1 || !(bk_inv > 0.0f) || !isfinite(bk_inv)) s_multi = 1;  // benign race: all write 1
   }
   __syncthreads();
   const bool use_buckets = s_multi == 0;  // block-uniform
 
-  const int lane = threadIdx.x & 63;
-  // wave-uniform from here to the stores: the vector, its request, page and
-  // slot are scalar values (the host bounds n_vec by INT32_MAX)
-  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int vec0 = ((int)blockIdx.x * kWavesPerBlock + wave) * kVecPerWave;
-  if (vec0 >= n_vec) return;  // the whole wave
-  const int nv = min(kVecPerWave, n_vec - vec0);
-
-  const uint64_t* xw = reinterpret_cast<const uint64_t*>(x);
-  uint64_t raw[kVecPerWave];
+  const int lane = tid & 63;
+  const RowLane rl(lane & 15);
+  const int g = lane >> 4;  // vector of the batch
+  // (the table is aligned to its size: an entry's address is base | bits | copy)
+  const uint32_t copy = (uint32_t)(uintptr_t)&bucket[0][lane & (kCopies - 1)];
+  float s[2][8];  // the lane's signs
 #pragma unroll
-  for (int v = 0; v < kVecPerWave; ++v)
-    if (v < nv) raw[v] = __builtin_nontemporal_load(&xw[(int64_t)(vec0 + v) * (kD / 4) + lane]);
-  const float4 s = reinterpret_cast<const float4*>(signs)[lane];
-  int row_cur = vec0 / Hkv, kv_cur = vec0 - row_cur * Hkv;  // of the next vector
-  int row_done = -1, page_row = -1, slot_in_page = 0;       // the looked-up row
-
+  for (int h = 0; h < 2; ++h)
 #pragma unroll
-  for (int v = 0; v < kVecPerWave; ++v) {
-    if (v >= nv) break;
-    const float2 f01 = h2_to_f2((uint32_t)raw[v]), f23 = h2_to_f2((uint32_t)(raw[v] >> 32));
+    for (int i = 0; i < 8; ++i) s[h][i] = signs[128 * h + 8 * rl.chunk + i];
 
-    // norm: squares of fp16 values are exact in float32
-    float ss = f01.x * f01.x + f01.y * f01.y + f23.x * f23.x + f23.y * f23.y;
-    ss += xor_lane<32>(ss);
-    ss += xor_lane<16>(ss);
-    ss += xor_lane<8>(ss);
-    ss += xor_lane<4>(ss);
-    ss += xor_lane<2>(ss);
-    ss += xor_lane<1>(ss);
-    const float rho = sqrtf(ss);
-
-    // H_256 S x: two stages in the lane, six across lanes
-    float e0 = s.x * f01.x, e1 = s.y * f01.y, e2 = s.z * f23.x, e3 = s.w * f23.y;
-    {
-      const float a0 = e0 + e1, a1 = e0 - e1, a2 = e2 + e3, a3 = e2 - e3;
-      e0 = a0 + a2; e1 = a1 + a3; e2 = a0 - a2; e3 = a1 - a3;
+  // wave-uniform: the batches wave, wave + W, ... (the host bounds n_vec by
+  // INT32_MAX)
+  const int W = (int)gridDim.x * kWavesPerBlock;
+  int batch = (int)blockIdx.x * kWavesPerBlock + __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n_batch = (n_vec - 1) / kBatch + 1;
+  if (batch >= n_batch) return;
+  auto load = [&](int bt, u32x4 (&r)[2]) {
+    const int64_t vec = min(bt * kBatch + g, n_vec - 1);  // past the end: the last vector again
+    const u32x4* src = x + vec * (kD / 8) + rl.chunk;
+    r[0] = __builtin_nontemporal_load(src);
+    r[1] = __builtin_nontemporal_load(src + kD / 16);
+  };
+  // request and logical position of a row: (table row, position, -1 if none)
+  auto row_pos = [&](int row, int& req) {
+    int32_t lo = 0, hi = B;  // request: largest b with cu_tok[b] <= row
+    while (hi - lo > 1) {
+      const int32_t mid = (lo + hi) >> 1;
+      if (cu_tok[mid] <= row) lo = mid; else hi = mid;
     }
-    stage<1>(e0, e1, e2, e3, lane);
-    stage<2>(e0, e1, e2, e3, lane);
-    stage<4>(e0, e1, e2, e3, lane);
-    stage<8>(e0, e1, e2, e3, lane);
-    stage<16>(e0, e1, e2, e3, lane);
-    stage<32>(e0, e1, e2, e3, lane);
-    // rotated unit vector y = H S x / (16 rho), by one rounded reciprocal
-    const float inv = rho > 0.0f ? __fdiv_rn(1.0f, rho * 16.0f) : 0.0f;
-    const float y[4] = {e0 * inv, e1 * inv, e2 * inv, e3 * inv};
+    req = lo;
+    const int64_t pos = (int64_t)start_pos[lo] + (row - cu_tok[lo]);
+    return pos >= 0 && pos < (int64_t)max_pages * P ? (int)pos : -1;
+  };
 
-    uint32_t q = 0;  // four 4-bit indices: element 4 lane + j at bits 4j
+  u32x4 next[2];
+  load(batch, next);
+  for (;;) {
+    const int vec0 = batch * kBatch;
+    const u32x4 raw[2] = {next[0], next[1]};
+    const bool more = n_batch - batch > W;
+    if (more) load(batch + W, next);
+
+    // destination (first step: the row's position; its page is read below)
+    const int row0 = vec0 / Hkv, kv0 = vec0 - row0 * Hkv;
+    const bool one_row = kv0 + kBatch <= Hkv;
+    int req, pos, kv = kv0 + g;
+    if (one_row) {
+      pos = row_pos(row0, req);
+    } else {
+      const int vec = vec0 + g, row = vec / Hkv;
+      kv = vec - row * Hkv;
+      pos = vec < n_vec ? row_pos(row, req) : -1;
+    }
+    const int lp = pos >= 0 ? pos / P : 0;
+    const int page = pos >= 0 ? block_tables[(int64_t)req * max_pages + lp] : -1;
+
+    // stage 0 with the signs; squares of fp16 values are exact in float32.
+    // The sums of squares: groups of four elements, then element index bits
+    // 7, 6, .. 2 in turn
+    float e[2][8], ss[2][2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const uint32_t w = raw[h][i];  // (a value: bit_cast of the vector's element takes element 0)
+        const h2 v = __builtin_bit_cast(h2, w);
+        const float f0 = (float)v.x, f1 = (float)v.y;
+        const float t1 = f1 * s[h][2 * i + 1];
+        e[h][2 * i] = fmaf(f0, s[h][2 * i], t1);
+        e[h][2 * i + 1] = fmaf(f0, s[h][2 * i], -t1);
+        float& q = ss[h][i >> 1];
+        q = (i & 1) ? fmaf(f0, f0, q) : f0 * f0;
+        q = fmaf(f1, f1, q);
+      }
+    }
+    float n0 = ss[0][0] + ss[1][0], n1 = ss[0][1] + ss[1][1];
+    n0 += partner<3>(n0); n1 += partner<3>(n1);
+    n0 += partner<2>(n0); n1 += partner<2>(n1);
+    n0 += partner<1>(n0); n1 += partner<1>(n1);
+    n0 += partner<0>(n0); n1 += partner<0>(n1);
+    const float rho = sqrtf(n0 + n1);
+
+    fwht_from1(e, rl);
+    // rotated unit vector y = H S x / (16 rho), by one rounded reciprocal
+    const float inv = rl.sign * (rho > 0.0f ? __fdiv_rn(1.0f, rho * 16.0f) : 0.0f);
+
+    uint32_t q[2] = {0, 0};  // eight 4-bit indices each, the first in the low bits
     if (use_buckets) {
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const float2 e = bucket[bucket_of(y[j])];
-        const int idx = __builtin_bit_cast(int, e.x) + (y[j] > e.y ? 1 : 0);
-        q |= (uint32_t)idx << (4 * j);
-      }
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int i = 7; i >= 0; --i) {
+          const float y = e[h][i] * inv;
+          const f32x2 en = *reinterpret_cast<const __attribute__((address_space(3))) f32x2*>(
+              (bucket_bits(y) & kMask) | copy);
+          const float b = en.x, t = en.y;
+          const uint32_t below = __builtin_bit_cast(uint32_t, b);
+          q[h] = (q[h] << 4) + below + (y > t ? 1u : 0u);
+        }
     } else {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      // off = 4 x the number of thresholds strictly below y[j] found so far
-      // (a byte offset, so each level's read takes its constant part as the
-      // instruction's offset)
-      int off = 0;
+      for (int h = 0; h < 2; ++h)
 #pragma unroll
-      for (int step = 8; step >= 1; step >>= 1) {
-        const float t = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(thr) + off +
-                                                        4 * (step - 1));
-        off += y[j] > t ? 4 * step : 0;
-      }
-      q |= (uint32_t)(off >> 2) << (4 * j);
+        for (int i = 7; i >= 0; --i) {
+          // off = 4 x the number of thresholds strictly below y found so far
+          // (a byte offset, so each level's read takes its constant part as
+          // the instruction's offset)
+          const float y = e[h][i] * inv;
+          int off = 0;
+#pragma unroll
+          for (int step = 8; step >= 1; step >>= 1) {
+            const float t = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(thr) + off +
+                                                            4 * (step - 1));
+            off += y > t ? 4 * step : 0;
+          }
+          q[h] = (q[h] << 4) + (uint32_t)(off >> 2);
+        }
     }
-    }
-    // word w = elements 8w .. 8w + 7: lanes 2w (low half) and 2w + 1
-    const uint32_t partner = __builtin_bit_cast(uint32_t, xor_lane<1>(__builtin_bit_cast(float, q)));
-    const uint32_t word = q | (partner << 16);
 
-    // (row, kv) of this vector; the row's destination is looked up once per
-    // row (the vectors of a wave are consecutive: Hkv of them per row)
-    const int kv = kv_cur;
-    if (++kv_cur == Hkv) kv_cur = 0;
-    if (row_cur != row_done) {
-      row_done = row_cur;
-      int32_t lo = 0, hi = B;  // request: largest b with cu_tok[b] <= row
-      while (hi - lo > 1) {
-        const int32_t mid = (lo + hi) >> 1;
-        if (cu_tok[mid] <= row_cur) lo = mid; else hi = mid;
-      }
-      const int64_t pos = (int64_t)start_pos[lo] + (row_cur - cu_tok[lo]);
-      page_row = -1;
-      if (pos >= 0 && pos < (int64_t)max_pages * P) {
-        const int lp = (int)pos / P;
-        page_row = block_tables[(int64_t)lo * max_pages + lp];
-        slot_in_page = (int)pos - lp * P;
-      }
+    if (vec0 + g < n_vec && (unsigned)page < (unsigned)NP) {
+      const int64_t slot = ((int64_t)page * Hkv + kv) * P + (pos - lp * P);
+      uint32_t* dst = words + slot * (kD / 8) + rl.chunk;
+      dst[0] = q[0];
+      dst[kD / 16] = q[1];
+      if ((lane & 15) == 0) norms[slot] = __float2half_rn(rho);
     }
-    if (kv_cur == 0) ++row_cur;
-    if (page_row < 0 || page_row >= NP) continue;
-    const int64_t slot = ((int64_t)page_row * Hkv + kv) * P + slot_in_page;
-    if ((lane & 1) == 0) words[slot * (kD / 8) + (lane >> 1)] = word;
-    if (lane == 0) norms[slot] = __float2half_rn(rho);
+    if (!more) return;
+    batch += W;
   }
 }
 
@@ -229,13 +326,15 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void tq4_encode_kernel(
 // page lookup, index unpacking, centroid lookup, inverse rotation, norm
 // restoration in one kernel): x_hat = rho_hat S H_256 c[z] / 16 for KV heads
 // kv0 .. kv0 + g - 1 at logical positions 0 .. n - 1 of one request, written
-// as contiguous fp16 [g][n][256] K (blockIdx.z = 0) or V operands.  One wave
-// per vector, kVecPerWave vectors per wave with their loads issued together;
-// lane l holds elements 4l .. 4l + 3 (its half of index word l / 2), looks
-// their centroids up in LDS and runs the same eight butterfly stages as the
-// encoder (H_256 is symmetric), then multiplies by its signs and rho_hat / 16
-// (fp32) and writes 8 bytes, so a vector's 512 bytes leave in one coalesced
-// store.  A page ID outside the pool gives zeros.
+// as contiguous fp16 [g][n][256] K (blockIdx.z = 0) or V operands.  Four
+// vectors per wave at a time, as in the encoder (H_256 is symmetric): lane c of
+// a row of 16 holds index words c and 16 + c (elements 8c .. and 128 + 8c ..),
+// looks their centroids up in LDS (16 words in 16 banks: no collisions), runs
+// the eight butterfly stages, then multiplies by rho_hat / 16 (fp32) and its
+// signs and stores two 16-byte pieces; a vector's 512 bytes are contiguous.  A
+// page ID outside the pool gives zeros.
+constexpr int kRecBatches = 4;  // batches per wave, their loads issued together
+
 __global__ __launch_bounds__(64 * kWavesPerBlock) void tq4_reconstruct_kernel(
     const uint32_t* __restrict__ k_words, const __half* __restrict__ k_norms,
     const uint32_t* __restrict__ v_words, const __half* __restrict__ v_norms,
@@ -244,7 +343,6 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void tq4_reconstruct_kernel(
     int Hkv, int P, int NP, uint2* __restrict__ k_out, uint2* __restrict__ v_out) {
   __shared__ float cent[kLevels];
   if (threadIdx.x < kLevels) cent[threadIdx.x] = centroids[threadIdx.x];
-  __syncthreads();
   const bool is_v = blockIdx.z != 0;
   const uint32_t* words = is_v ? v_words : k_words;
   const __half* norms = is_v ? v_norms : k_norms;
@@ -253,53 +351,77 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void tq4_reconstruct_kernel(
   const int kv = kv0 + j;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int t0 = ((int)blockIdx.x * kWavesPerBlock + wave) * kVecPerWave;
-  if (t0 >= n) return;  // the whole wave
-  const int nv = min(kVecPerWave, n - t0);
-  const float4 sg = reinterpret_cast<const float4*>(is_v ? v_signs : k_signs)[lane];
+  constexpr int kPerWave = kRecBatches * kBatch;
+  const int t0 = ((int)blockIdx.x * kWavesPerBlock + wave) * kPerWave;
+  const RowLane rl(lane & 15);
+  const int g = lane >> 4;
 
-  uint32_t wd[kVecPerWave];
-  float rho[kVecPerWave];
-  bool ok[kVecPerWave];
+  // the wave's positions lie in one page when the page size is a multiple of
+  // them (one scalar lookup), otherwise each is looked up
+  uint32_t wd[kRecBatches][2];
+  float rho[kRecBatches];
+  bool ok[kRecBatches];
+  const bool one_page = P % kPerWave == 0;
+  const int page0 = one_page && t0 < n ? table[t0 / P] : -1;
+  const int slot0 = one_page ? t0 % P : 0;
 #pragma unroll
-  for (int v = 0; v < kVecPerWave; ++v) {
-    wd[v] = 0u;
+  for (int v = 0; v < kRecBatches; ++v) {
+    const int t = t0 + kBatch * v + g;
+    int page = page0, slot = slot0 + kBatch * v + g;
+    if (!one_page) {
+      page = t < n ? table[t / P] : -1;
+      slot = t % P;
+    }
+    ok[v] = t < n && (unsigned)page < (unsigned)NP;
+    wd[v][0] = wd[v][1] = 0u;
     rho[v] = 0.0f;
-    ok[v] = false;  // outside the pool: zeros
-    if (v < nv) {
-      const int t = t0 + v;
-      const int page = table[t / P];  // wave-uniform
-      ok[v] = (unsigned)page < (unsigned)NP;
-      if (ok[v]) {
-        const int64_t vec = ((int64_t)page * Hkv + kv) * P + (t % P);
-        wd[v] = words[vec * (kD / 8) + (lane >> 1)];
-        rho[v] = __half2float(norms[vec]);
-      }
+    if (ok[v]) {
+      const int64_t vec = ((int64_t)page * Hkv + kv) * P + slot;
+      wd[v][0] = words[vec * (kD / 8) + rl.chunk];
+      wd[v][1] = words[vec * (kD / 8) + kD / 16 + rl.chunk];
+      rho[v] = __half2float(norms[vec]);
     }
   }
+  // signs of the lane's elements times the transform's, as bits of fp16 pairs
+  const float* signs = is_v ? v_signs : k_signs;
+  uint32_t sx[2][4];
 #pragma unroll
-  for (int v = 0; v < kVecPerWave; ++v) {
-    if (v >= nv) break;
-    const uint32_t q = wd[v] >> (16 * (lane & 1));  // element 4 lane + i at bits 4 i
-    float e0 = cent[q & 15u], e1 = cent[(q >> 4) & 15u];
-    float e2 = cent[(q >> 8) & 15u], e3 = cent[(q >> 12) & 15u];
-    {
-      const float a0 = e0 + e1, a1 = e0 - e1, a2 = e2 + e3, a3 = e2 - e3;
-      e0 = a0 + a2; e1 = a1 + a3; e2 = a0 - a2; e3 = a1 - a3;
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float* sp = signs + 128 * h + 8 * rl.chunk + 2 * i;
+      sx[h][i] = (__builtin_bit_cast(uint32_t, sp[0] * rl.sign) >> 31 << 15) |
+                 (__builtin_bit_cast(uint32_t, sp[1] * rl.sign) & 0x80000000u);
     }
-    stage<1>(e0, e1, e2, e3, lane);
-    stage<2>(e0, e1, e2, e3, lane);
-    stage<4>(e0, e1, e2, e3, lane);
-    stage<8>(e0, e1, e2, e3, lane);
-    stage<16>(e0, e1, e2, e3, lane);
-    stage<32>(e0, e1, e2, e3, lane);
+  __syncthreads();
+#pragma unroll
+  for (int v = 0; v < kRecBatches; ++v) {
+    const int t = t0 + kBatch * v + g;
+    if (t0 + kBatch * v >= n) break;  // the whole wave
+    float e[2][8];
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int i = 0; i < 8; i += 2) {
+        const uint32_t w = wd[v][h];
+        const float c0 = cent[(w >> (4 * i)) & 15u], c1 = cent[(w >> (4 * i + 4)) & 15u];
+        e[h][i] = c0 + c1;
+        e[h][i + 1] = c0 - c1;
+      }
+    fwht_from1(e, rl);
     const float f = rho[v] * 0.0625f;
-    uint2 o = make_uint2(0u, 0u);
-    if (ok[v]) {
-      o.x = __builtin_bit_cast(uint32_t, __floats2half2_rn(sg.x * e0 * f, sg.y * e1 * f));
-      o.y = __builtin_bit_cast(uint32_t, __floats2half2_rn(sg.z * e2 * f, sg.w * e3 * f));
+    u32x4 o[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        o[h][i] = ok[v] ? __builtin_bit_cast(uint32_t, __floats2half2_rn(e[h][2 * i] * f, e[h][2 * i + 1] * f)) ^ sx[h][i]
+                        : 0u;
+    if (t < n) {
+      u32x4* dst = reinterpret_cast<u32x4*>(out + ((int64_t)j * n + t) * (kD / 4)) + rl.chunk;
+      dst[0] = o[0];
+      dst[kD / 16] = o[1];
     }
-    out[((int64_t)j * n + t0 + v) * (kD / 4) + lane] = o;
   }
 }
 
@@ -314,8 +436,8 @@ hipError_t launch_tq4_reconstruct(const jf_kv_layout& L, const void* k_words, co
                                   int32_t num_heads, void* k_out, void* v_out,
                                   hipStream_t stream) {
   if (n_pos == 0) return hipSuccess;
-  constexpr int kPerBlock = kWavesPerBlock * kVecPerWave;
-  dim3 grid((unsigned)((n_pos + kPerBlock - 1) / kPerBlock), (unsigned)num_heads, 2);
+  constexpr int kPerBlock = kWavesPerBlock * kRecBatches * kBatch;
+  dim3 grid((unsigned)((n_pos + (int64_t)kPerBlock - 1) / kPerBlock), (unsigned)num_heads, 2);
   hipLaunchKernelGGL(tq4_reconstruct_kernel, grid, dim3(64 * kWavesPerBlock), 0, stream,
                      static_cast<const uint32_t*>(k_words), static_cast<const __half*>(k_norms),
                      static_cast<const uint32_t*>(v_words), static_cast<const __half*>(v_norms),
@@ -330,12 +452,16 @@ hipError_t launch_tq4_encode(const jf_kv_layout& L, void* words, void* norms, co
                              const int32_t* start_pos, const int32_t* block_tables, int32_t B,
                              int32_t max_pages, int32_t total_tok, hipStream_t stream) {
   const int64_t n_vec = (int64_t)total_tok * L.num_kv_heads;
-  constexpr int kPerBlock = kWavesPerBlock * kVecPerWave;
-  const int64_t blocks = (n_vec + kPerBlock - 1) / kPerBlock;
+  // persistent: at most kBlocksPerCu blocks per CU, whose waves take batches in
+  // turn (each block builds the bucket table once)
+  constexpr int kPerBlock = kWavesPerBlock * kBatch;
+  constexpr int64_t kBlocksPerCu = 8;
+  const int64_t blocks = std::min<int64_t>((n_vec + kPerBlock - 1) / kPerBlock,
+                                           kBlocksPerCu * num_cus());
   if (n_vec > 0x7fffffffLL) return hipErrorInvalidValue;
   hipLaunchKernelGGL(tq4_encode_kernel, dim3((unsigned)blocks), dim3(64 * kWavesPerBlock), 0,
                      stream, static_cast<uint32_t*>(words), static_cast<__half*>(norms),
-                     static_cast<const uint2*>(x), signs, centroids, cu_tok, start_pos,
+                     static_cast<const u32x4*>(x), signs, centroids, cu_tok, start_pos,
                      block_tables, B, max_pages, L.num_kv_heads, L.page_size, L.num_pages,
                      (int)n_vec);
   return hipGetLastError();
