@@ -25,7 +25,10 @@
 // butterfly reduction ends with the same sum.
 //
 // What bounds the kernels: vector issue, then HBM.  Per vector ~80 vector
-// instructions and 4 LDS reads (~146 and ~25 before this layout).
+// instructions and 4 LDS reads (~146 and ~25 with a lane per four elements).
+// K and V of 262,143 rows of 4 heads: 460 -> 314 us (2.9 -> 4.3 TB/s);
+// reconstruction of 2 heads over 196,608 positions: 169 -> 111 us (3.0 -> 4.5
+// TB/s; a large copy reaches 5.1).
 //
 // Index of a coordinate: the number of midpoint thresholds between adjacent
 // centroids that it strictly exceeds (a coordinate on a threshold keeps the
@@ -65,7 +68,6 @@ constexpr int kLevels = 16;
 constexpr int kBuckets = 64;     // index buckets (at most one threshold each)
 constexpr int kCopies = 32;      // of the bucket table: one per pair of LDS banks
 
-typedef _Float16 h2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // Rows and operands are 8-byte aligned, by contract; global memory takes a
@@ -96,6 +98,38 @@ struct RowLane {
     }
   }
 };
+
+// Sums of the fp16 halves (x, y) of a word in float32, one mixed-precision fma
+// each (the compiler converts both halves first): x + y, x - y, and q + x * x +
+// y * y (the squares exact, two roundings).
+__device__ __forceinline__ float add_halves(uint32_t w) {
+  float r;
+  asm("v_fma_mix_f32 %0, %1, 1.0, %1 op_sel:[0,0,1] op_sel_hi:[1,0,1]" : "=v"(r) : "v"(w));
+  return r;
+}
+__device__ __forceinline__ float sub_halves(uint32_t w) {
+  float r;
+  asm("v_fma_mix_f32 %0, %1, 1.0, -%1 op_sel:[0,0,1] op_sel_hi:[1,0,1]" : "=v"(r) : "v"(w));
+  return r;
+}
+__device__ __forceinline__ float add_squares(uint32_t w, float q) {
+  asm("v_fma_mix_f32 %0, %1, %1, %0 op_sel_hi:[1,1,0]" : "+v"(q) : "v"(w));
+  asm("v_fma_mix_f32 %0, %1, %1, %0 op_sel:[1,1,0] op_sel_hi:[1,1,0]" : "+v"(q) : "v"(w));
+  return q;
+}
+
+// Sign bits of signs[element] * by for a lane's elements, as bits of fp16 pairs.
+__device__ __forceinline__ void sign_bits(uint32_t (&sx)[2][4], const float* signs, int chunk,
+                                          float by) {
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const float* sp = signs + 128 * h + 8 * chunk + 2 * i;
+      sx[h][i] = (__builtin_bit_cast(uint32_t, sp[0] * by) >> 31 << 15) |
+                 (__builtin_bit_cast(uint32_t, sp[1] * by) & 0x80000000u);
+    }
+}
 
 // The four exchanging stages (element index bits 3..6): one instruction per
 // element and stage.  Written out, since the compiler makes each a move with
@@ -195,11 +229,8 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void tq4_encode_kernel(
   const int g = lane >> 4;  // vector of the batch
   // (the table is aligned to its size: an entry's address is base | bits | copy)
   const uint32_t copy = (uint32_t)(uintptr_t)&bucket[0][lane & (kCopies - 1)];
-  float s[2][8];  // the lane's signs
-#pragma unroll
-  for (int h = 0; h < 2; ++h)
-#pragma unroll
-    for (int i = 0; i < 8; ++i) s[h][i] = signs[128 * h + 8 * rl.chunk + i];
+  uint32_t sx[2][4];  // the signs of the lane's elements, as bits of fp16 pairs
+  sign_bits(sx, signs, rl.chunk, 1.0f);
 
   // wave-uniform: the batches wave, wave + W, ... (the host bounds n_vec by
   // INT32_MAX)
@@ -207,45 +238,49 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void tq4_encode_kernel(
   int batch = (int)blockIdx.x * kWavesPerBlock + __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n_batch = (n_vec - 1) / kBatch + 1;
   if (batch >= n_batch) return;
-  auto load = [&](int bt, u32x4 (&r)[2]) {
-    const int64_t vec = min(bt * kBatch + g, n_vec - 1);  // past the end: the last vector again
-    const u32x4* src = x + vec * (kD / 8) + rl.chunk;
-    r[0] = __builtin_nontemporal_load(src);
-    r[1] = __builtin_nontemporal_load(src + kD / 16);
+  u32x4 raw[2];
+  const int lane_x = g * (kD / 8) + rl.chunk;       // in a batch of rows
+  const int lane_w = g * P * (kD / 8) + rl.chunk;   // in the words of neighbouring KV heads
+  auto load = [&](int bt) {
+    const u32x4* src = x + (int64_t)bt * (kBatch * (kD / 8));
+    // (past the end: the last vector again)
+    const int at = n_vec - bt * kBatch >= kBatch
+                       ? lane_x
+                       : min(g, n_vec - bt * kBatch - 1) * (kD / 8) + rl.chunk;
+    raw[0] = __builtin_nontemporal_load(src + at);
+    raw[1] = __builtin_nontemporal_load(src + at + kD / 16);
   };
-  // request and logical position of a row: (table row, position, -1 if none)
-  auto row_pos = [&](int row, int& req) {
+  // slot of KV head 0 of a row, (page * Hkv) * P + slot in the page; -1: none
+  auto row_slot = [&](int row) -> int64_t {
     int32_t lo = 0, hi = B;  // request: largest b with cu_tok[b] <= row
     while (hi - lo > 1) {
       const int32_t mid = (lo + hi) >> 1;
       if (cu_tok[mid] <= row) lo = mid; else hi = mid;
     }
-    req = lo;
     const int64_t pos = (int64_t)start_pos[lo] + (row - cu_tok[lo]);
-    return pos >= 0 && pos < (int64_t)max_pages * P ? (int)pos : -1;
+    if (pos < 0 || pos >= (int64_t)max_pages * P) return -1;
+    const int lp = (int)pos / P;
+    const int page = block_tables[(int64_t)lo * max_pages + lp];
+    if ((unsigned)page >= (unsigned)NP) return -1;
+    return (int64_t)page * Hkv * P + ((int)pos - lp * P);
   };
 
-  u32x4 next[2];
-  load(batch, next);
+  load(batch);
   for (;;) {
     const int vec0 = batch * kBatch;
-    const u32x4 raw[2] = {next[0], next[1]};
     const bool more = n_batch - batch > W;
-    if (more) load(batch + W, next);
 
-    // destination (first step: the row's position; its page is read below)
+    // destination: wave-uniform where the batch is heads kv0 .. of one row
     const int row0 = vec0 / Hkv, kv0 = vec0 - row0 * Hkv;
     const bool one_row = kv0 + kBatch <= Hkv;
-    int req, pos, kv = kv0 + g;
+    int64_t slot_row = -1, slot_vec = -1;
     if (one_row) {
-      pos = row_pos(row0, req);
-    } else {
-      const int vec = vec0 + g, row = vec / Hkv;
-      kv = vec - row * Hkv;
-      pos = vec < n_vec ? row_pos(row, req) : -1;
+      slot_row = row_slot(row0);
+    } else if (vec0 + g < n_vec) {
+      const int row = (vec0 + g) / Hkv;
+      slot_vec = row_slot(row);
+      if (slot_vec >= 0) slot_vec += (int64_t)(vec0 + g - row * Hkv) * P;
     }
-    const int lp = pos >= 0 ? pos / P : 0;
-    const int page = pos >= 0 ? block_tables[(int64_t)req * max_pages + lp] : -1;
 
     // stage 0 with the signs; squares of fp16 values are exact in float32.
     // The sums of squares: groups of four elements, then element index bits
@@ -255,17 +290,14 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void tq4_encode_kernel(
     for (int h = 0; h < 2; ++h) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const uint32_t w = raw[h][i];  // (a value: bit_cast of the vector's element takes element 0)
-        const h2 v = __builtin_bit_cast(h2, w);
-        const float f0 = (float)v.x, f1 = (float)v.y;
-        const float t1 = f1 * s[h][2 * i + 1];
-        e[h][2 * i] = fmaf(f0, s[h][2 * i], t1);
-        e[h][2 * i + 1] = fmaf(f0, s[h][2 * i], -t1);
+        const uint32_t w = raw[h][i] ^ sx[h][i];
+        e[h][2 * i] = add_halves(w);
+        e[h][2 * i + 1] = sub_halves(w);
         float& q = ss[h][i >> 1];
-        q = (i & 1) ? fmaf(f0, f0, q) : f0 * f0;
-        q = fmaf(f1, f1, q);
+        q = add_squares(w, (i & 1) ? q : 0.0f);
       }
     }
+    if (more) load(batch + W);  // the registers are free; it returns during the transform
     float n0 = ss[0][0] + ss[1][0], n1 = ss[0][1] + ss[1][1];
     n0 += partner<3>(n0); n1 += partner<3>(n1);
     n0 += partner<2>(n0); n1 += partner<2>(n1);
@@ -310,12 +342,19 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void tq4_encode_kernel(
         }
     }
 
-    if (vec0 + g < n_vec && (unsigned)page < (unsigned)NP) {
-      const int64_t slot = ((int64_t)page * Hkv + kv) * P + (pos - lp * P);
-      uint32_t* dst = words + slot * (kD / 8) + rl.chunk;
+    if (one_row) {
+      if (slot_row >= 0) {
+        const int64_t slot0 = slot_row + (int64_t)kv0 * P;
+        uint32_t* dst = words + slot0 * (kD / 8);
+        dst[lane_w] = q[0];
+        dst[lane_w + kD / 16] = q[1];
+        if ((lane & 15) == 0) (norms + slot0)[g * P] = __float2half_rn(rho);
+      }
+    } else if (slot_vec >= 0) {
+      uint32_t* dst = words + slot_vec * (kD / 8) + rl.chunk;
       dst[0] = q[0];
       dst[kD / 16] = q[1];
-      if ((lane & 15) == 0) norms[slot] = __float2half_rn(rho);
+      if ((lane & 15) == 0) norms[slot_vec] = __float2half_rn(rho);
     }
     if (!more) return;
     batch += W;
@@ -385,14 +424,7 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void tq4_reconstruct_kernel(
   // signs of the lane's elements times the transform's, as bits of fp16 pairs
   const float* signs = is_v ? v_signs : k_signs;
   uint32_t sx[2][4];
-#pragma unroll
-  for (int h = 0; h < 2; ++h)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const float* sp = signs + 128 * h + 8 * rl.chunk + 2 * i;
-      sx[h][i] = (__builtin_bit_cast(uint32_t, sp[0] * rl.sign) >> 31 << 15) |
-                 (__builtin_bit_cast(uint32_t, sp[1] * rl.sign) & 0x80000000u);
-    }
+  sign_bits(sx, signs, rl.chunk, rl.sign);
   __syncthreads();
 #pragma unroll
   for (int v = 0; v < kRecBatches; ++v) {
@@ -453,7 +485,9 @@ hipError_t launch_tq4_encode(const jf_kv_layout& L, void* words, void* norms, co
                              int32_t max_pages, int32_t total_tok, hipStream_t stream) {
   const int64_t n_vec = (int64_t)total_tok * L.num_kv_heads;
   // persistent: at most kBlocksPerCu blocks per CU, whose waves take batches in
-  // turn (each block builds the bucket table once)
+  // turn (each block builds the bucket table once; 5, 6, 8 and 12 blocks: 327,
+  // 321, 314 and 312 us for the append above, 37.1, 36.6, 36.7 and 38.5 us for
+  // 20,000 rows)
   constexpr int kPerBlock = kWavesPerBlock * kBatch;
   constexpr int64_t kBlocksPerCu = 8;
   const int64_t blocks = std::min<int64_t>((n_vec + kPerBlock - 1) / kPerBlock,
