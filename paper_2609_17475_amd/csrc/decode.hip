@@ -107,6 +107,7 @@ constexpr int head_slots() {
   return hs < waves_for<D>() ? hs : waves_for<D>();
 }
 constexpr int kMaxStages = JF_DECODE_STAGES;  // LDS ring depth per wave (at most)
+constexpr int kPairStages = 2;                // ... of blocks that share a CU two and two
 
 __device__ __forceinline__ h2 as_h2(uint32_t u) { return __builtin_bit_cast(h2, u); }
 
@@ -476,8 +477,12 @@ __device__ void combine_splits(const float* ws, __half* out, int b, int Hq, int 
 // without waiting, and writes the same bytes into its LDS stage once that
 // row's loads have landed (they may still see the slot's previous bytes);
 // no other block reads that page.
-template <int D, int G, bool APPEND, int CS>
-__global__ __launch_bounds__(kMaxThreads) void decode_kernel(
+//
+// RING: stages of a wave's ring (at most).  A block with rings of three fills
+// a CU; with two (kPairStages), two blocks share one, and one's start, merge
+// and combine pass under the other's page loop (see launch_cs for when).
+template <int D, int G, bool APPEND, int CS, int RING>
+__global__ __launch_bounds__(kMaxThreads, RING == kPairStages && D == 128 ? 4 : 1) void decode_kernel(
     uint8_t* __restrict__ k_codes, uint32_t* __restrict__ k_meta,
     uint8_t* __restrict__ v_codes, uint32_t* __restrict__ v_meta,
     const uint4* __restrict__ k_new, const uint4* __restrict__ v_new,
@@ -501,7 +506,7 @@ __global__ __launch_bounds__(kMaxThreads) void decode_kernel(
   constexpr int kStageBytes = 2 * KB + 2 * kMetaBytes;
   constexpr int DMAS_PER_ROW = 2 * K_DMAS + 2 * META_DMAS;
   constexpr int kFit = (kRingBudget - 16) / (kWaves * kStageBytes);
-  constexpr int kStages = kFit < kMaxStages ? kFit : kMaxStages;
+  constexpr int kStages = kFit < RING ? kFit : RING;
   static_assert(kStages >= 2, "ring depth");
   constexpr int kHeadSlots = head_slots<D, G>();  // heads per column set
   constexpr int NS = 16 / kHeadSlots;      // column slots per head
@@ -1261,7 +1266,23 @@ hipError_t launch_cs(const jf_kv_layout& L, const jf_kv_pool_ptrs& pool, const v
   dim3 grid = n_hchunks == 1
                   ? dim3(split_cap, L.num_kv_heads, B)
                   : dim3((uint32_t)(((slots + kXcds - 1) / kXcds) * kXcds * n_hchunks), 1, B);
-  hipLaunchKernelGGL((decode_kernel<D, G, APPEND, CS>), grid, dim3(64 * waves_for<D>()), 0, stream,
+  // More blocks than CUs (a batch) and one column set: two blocks per CU where
+  // the tables give a split at most kPairPositions positions, so that one's
+  // fixed costs pass under the other's page loop; longer ones are bound by HBM
+  // and stream better with three stages per wave (at head_dim 256, with half
+  // the waves, two blocks always win).  The results are the same to the bit.
+  // Fused step, 32/8 heads, d = 128, three stages against pairs: 2 x 20K
+  // positions 25.8 / 21.1 us, 2 x 80K 47.5 / 44.5, 8 of 9K..30K 88.7 / 62.3,
+  // 2 x 130K 64.9 / 65.3, 196K + 131K 74.4 / 76.5; 24/4 heads, d = 256: 2 x 20K
+  // 37.1 / 28.9, 2 x 130K 118 / 98.  (Here at d = 64 two blocks fit anyway.)
+  constexpr bool kPairs = CS == 1 && D >= 128;
+  constexpr int64_t kPairPositions = 4096;
+  const bool pair =
+      kPairs && (int64_t)grid.x * grid.y * B > jfkv::num_cus() &&
+      (D > 128 || (int64_t)max_pages * L.page_size <= kPairPositions * split_cap);
+  const auto kernel = pair ? decode_kernel<D, G, APPEND, CS, kPairs ? kPairStages : kMaxStages>
+                           : decode_kernel<D, G, APPEND, CS, kMaxStages>;
+  hipLaunchKernelGGL(kernel, grid, dim3(64 * waves_for<D>()), 0, stream,
                      static_cast<uint8_t*>(pool.k_codes), static_cast<uint32_t*>(pool.k_meta),
                      static_cast<uint8_t*>(pool.v_codes), static_cast<uint32_t*>(pool.v_meta),
                      static_cast<const uint4*>(k_new), static_cast<const uint4*>(v_new),
