@@ -21,8 +21,7 @@
 // copy l from its own bank (random entries would otherwise collide in the LDS
 // banks), and 64 KiB-aligned, so that one byte permute of the index word
 // forms a lookup's address (the index byte is the address's second byte).
-// The table's 64 KiB hold q' before the page loop and the final rotation
-// after it.  The centroids are rounded to fp16 once (relative error
+// The table's 64 KiB hold the rows of the final rotation after the page loop.  The centroids are rounded to fp16 once (relative error
 // <= 2^-11); q' enters as an fp16 high part plus an fp16 low part.
 //
 // Matrix-core layout (v_mfma_f32_16x16x32_f16; lane (m, q4) = (lane % 16,
@@ -51,6 +50,7 @@
 #include <algorithm>
 
 #include "jfkv.h"
+#include "jfkv_fwht.h"
 #include "jfkv_internal.h"
 
 namespace {
@@ -97,20 +97,20 @@ __device__ __forceinline__ f32x4 mfma(h8 a, h8 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
 }
 
-// In-place Walsh-Hadamard transform (unnormalised, natural order) of n rows
-// of 256 floats in LDS, by the whole block.
-__device__ void fwht_rows(float* x, int n) {
-  for (int h = 1; h < kD; h <<= 1) {
-    for (int i = threadIdx.x; i < n * (kD / 2); i += kThreads) {
-      const int r = i / (kD / 2), k = i % (kD / 2);
-      float* row = x + r * kD;
-      const int a = (k / h) * (2 * h) + (k % h);
-      const float u = row[a], v = row[a + h];
-      row[a] = u + v;
-      row[a + h] = u - v;
+// The unnormalised Walsh-Hadamard transform of one 256-element row per 16
+// lanes (lane layout of jfkv_fwht.h); leaves rl.sign times the result.  In
+// registers: as eight in-place stages over LDS with a barrier each it took
+// 1.5 us at either end of every call.
+__device__ __forceinline__ void fwht_row(float (&e)[2][8], const jfkv::RowLane& rl) {
+#pragma unroll
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int i = 0; i < 8; i += 2) {
+      const float u = e[h][i], v = e[h][i + 1];
+      e[h][i] = u + v;
+      e[h][i + 1] = u - v;
     }
-    __syncthreads();
-  }
+  jfkv::fwht_from1(e, rl);
 }
 
 // Page-aligned split s of n_pages pages into S parts (remainder first).
@@ -137,11 +137,12 @@ __global__ __launch_bounds__(kThreads) void tq4_decode_kernel(
     float* __restrict__ ws, uint32_t* __restrict__ tickets, __half* __restrict__ out, int Hq,
     int Hkv, int P, int NP, int max_pages, int max_splits, int split_cap, float scale_log2) {
   // index byte -> fp16 centroids of its nibbles, 64 copies (the page loop);
-  // before and after the loop the same bytes hold q' and the final rotation
+  // after the loop the same bytes hold the rows to rotate back
   __shared__ __attribute__((aligned(65536))) uint32_t s_tab[256 * 64];
   float* const s_x = reinterpret_cast<float*>(s_tab);     // [kMaxCols][kD]
-  static_assert(kMaxCols * kD <= 256 * 64, "q' fits the table's bytes");
-  __shared__ float s_part[kParts][kMaxCols * (kD + 2)];  // per-wave partials (u, m, l)
+  static_assert(kMaxCols * kD <= 256 * 64, "the rows fit the table's bytes");
+  __shared__ __attribute__((aligned(16))) float s_part[kParts][kMaxCols * (kD + 2)];  // per-wave partials (u, m, l)
+  float* const s_q = s_part[0];                           // before the loop: q' [kMaxCols][kD]
   __shared__ h8 s_qop[8][2][64];                         // score B operands (q' high, low)
   __shared__ uint32_t s_ticket;
 
@@ -165,46 +166,6 @@ __global__ __launch_bounds__(kThreads) void tq4_decode_kernel(
   int pb, pe;
   split_range(n_pages, S, split, pb, pe);
   const int t_end = min(pe * P, L);
-
-  // ---- q' = H S q / 16 per query head (a negative scale negates it)
-  const float qsign = scale_log2 < 0.0f ? -1.0f : 1.0f;
-  for (int i = tid; i < gq * kD; i += kThreads) {
-    const int h = i / kD, d = i % kD;
-    s_x[i] = qsign * k_signs[d] * __half2float(q[((size_t)b * Hq + h0 + h) * kD + d]);
-  }
-  __syncthreads();
-  fwht_rows(s_x, gq);
-  // B operands in LDS (one 16-byte entry per lane, read back conflict-free):
-  // k-step kb, lane (col, q4): word 8 q4 + kb, dims 0..7 of it, as an
-  // fp16 high part and an fp16 low part; each wave fills one k-step
-#pragma unroll
-  for (int k2 = 0; k2 < 8 / kWaves; ++k2) {
-    const int kb = (8 / kWaves) * wave + k2;
-    const int w = 8 * q4 + kb;
-    const bool col_on = l16 < gq;
-    h8 hi, lo;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const int d = 8 * w + e;
-      const float v = s_x[min(l16, gq - 1) * kD + d] * 0.0625f;
-      const _Float16 vh = col_on ? (_Float16)v : (_Float16)0.0f;
-      hi[e] = vh;
-      lo[e] = col_on ? (_Float16)(v - (float)vh) : (_Float16)0.0f;
-    }
-    s_qop[kb][0][lane] = hi;
-    s_qop[kb][1][lane] = lo;
-  }
-  __syncthreads();  // q' is in the operands: its bytes become the table
-  // pair table: entry e holds c[e & 15] (low half) and c[e >> 4] (high half),
-  // copy c (0..63) at word 64 e + c
-  for (int i = tid; i < 256 * 64; i += kThreads) {
-    const int e = i >> 6;
-    const uint32_t lo = __builtin_bit_cast(uint16_t, (_Float16)centroids[e & 15]);
-    const uint32_t hi = __builtin_bit_cast(uint16_t, (_Float16)centroids[e >> 4]);
-    s_tab[i] = lo | (hi << 16);
-  }
-  __syncthreads();
-  const float kfold = fmaxf(fabsf(scale_log2), 1e-30f);  // |scale| in log2 units
 
   // ---- this wave's rows: split rows wave, wave + kWaves, ...
   const int rpp = P / kRowPos;  // rows per page
@@ -243,6 +204,75 @@ __global__ __launch_bounds__(kThreads) void tq4_decode_kernel(
     rb.kn = ld_nt(reinterpret_cast<const uint32_t*>(k_norms + vec0 + 8 * q4));
     rb.vn = ld_nt(reinterpret_cast<const uint32_t*>(v_norms + vec0 + 8 * q4));
   };
+
+  // the first row's data comes in while the table and the operands are made
+  RowBuf b0, b1;
+  if (my_rows > 0) load_row(0, b0);
+
+  // pair table: entry e holds c[e & 15] (low half) and c[e >> 4] (high half),
+  // copy c (0..63) at word 64 e + c.  A 16-byte store per lane covers entries
+  // 4 k .. 4 k + 3 (16 lanes each); wave w writes k = 8 w .. 8 w + 7, whose
+  // high centroids are c[2 w] and c[2 w + 1]
+  {
+    static_assert(kWaves == 8, "an eighth of the table per wave");
+    uint32_t lo[4], hi[2];
+#pragma unroll
+    for (int k = 0; k < 4; ++k)
+      lo[k] = __builtin_bit_cast(uint16_t, (_Float16)centroids[4 * k + q4]);
+#pragma unroll
+    for (int k = 0; k < 2; ++k)
+      hi[k] = (uint32_t)__builtin_bit_cast(uint16_t, (_Float16)centroids[2 * wave + k]) << 16;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      const uint32_t w = lo[k & 3] | hi[k >> 2];
+      reinterpret_cast<u32x4*>(s_tab)[(8 * wave + k) * 64 + lane] = u32x4{w, w, w, w};
+    }
+  }
+  // ---- q' = H S q / 16 per query head (a negative scale negates it): four
+  // heads per wave
+  const jfkv::RowLane rl(l16);
+  const float qsign = scale_log2 < 0.0f ? -1.0f : 1.0f;
+  for (int hq0 = 4 * wave; hq0 < gq; hq0 += 4 * kWaves) {
+    const int h = min(hq0 + q4, gq - 1);
+    float e[2][8];
+#pragma unroll
+    for (int hf = 0; hf < 2; ++hf) {
+      const int d0 = 128 * hf + 8 * rl.chunk;
+      const __half* src = q + ((size_t)b * Hq + h0 + h) * kD + d0;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) e[hf][i] = qsign * k_signs[d0 + i] * __half2float(src[i]);
+    }
+    fwht_row(e, rl);
+    if (hq0 + q4 < gq) {
+#pragma unroll
+      for (int hf = 0; hf < 2; ++hf)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) s_q[h * kD + 128 * hf + 8 * rl.chunk + i] = rl.sign * e[hf][i];
+    }
+  }
+  __syncthreads();
+  // B operands in LDS (one 16-byte entry per lane, read back conflict-free):
+  // k-step kb, lane (col, q4): word 8 q4 + kb, dims 0..7 of it, as an
+  // fp16 high part and an fp16 low part; each wave fills one k-step
+#pragma unroll
+  for (int k2 = 0; k2 < 8 / kWaves; ++k2) {
+    const int kb = (8 / kWaves) * wave + k2;
+    const int w = 8 * q4 + kb;
+    const bool col_on = l16 < gq;
+    h8 hi, lo;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int d = 8 * w + e;
+      const float v = s_q[min(l16, gq - 1) * kD + d] * 0.0625f;
+      const _Float16 vh = col_on ? (_Float16)v : (_Float16)0.0f;
+      hi[e] = vh;
+      lo[e] = col_on ? (_Float16)(v - (float)vh) : (_Float16)0.0f;
+    }
+    s_qop[kb][0][lane] = hi;
+    s_qop[kb][1][lane] = lo;
+  }
+  __syncthreads();
+  const float kfold = fmaxf(fabsf(scale_log2), 1e-30f);  // |scale| in log2 units
 
   // Lane l reads copy l (its own bank): the LDS address of entry e is
   // base + 256 e + 4 l with the table 64 KiB-aligned, i.e. the base's bytes
@@ -353,8 +383,6 @@ __global__ __launch_bounds__(kThreads) void tq4_decode_kernel(
     }
   };
 
-  RowBuf b0, b1;
-  if (my_rows > 0) load_row(0, b0);
   for (int r = 0; r < my_rows; r += 2) {
     if (r + 1 < my_rows) load_row(r + 1, b1);
     compute_row(b0, r);
@@ -444,6 +472,22 @@ __global__ __launch_bounds__(kThreads) void tq4_decode_kernel(
   __syncthreads();
   if (s_ticket != (uint32_t)(S - 1)) return;
   if (tid == 0) __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  // The records' values: a wave task is (head, half of the dims); lane (c, k) =
+  // (lane % 32, lane / 32) sums dims 128 half + 4 c .. + 3 over the splits k,
+  // k + 2, ..., kCh independent 16-byte loads at a time; those of the wave's
+  // first task are under way while the weights are made.
+  constexpr int kCh = 32;
+  auto load_records = [&](int task, int s0, f32x4 (&o)[kCh]) {
+    const auto rs = head_records(ws + ((size_t)b * Hq + h0 + (task >> 1)) * max_splits * (kD + 4), max_splits);
+    const int d0 = (kD / 2) * (task & 1) + 4 * (lane & 31);
+#pragma unroll
+    for (int i = 0; i < kCh; ++i) {  // past the end: a valid record, weight 0
+      const int s = min(s0 + 2 * i, S - 1);
+      o[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, (s * (kD + 4) + d0) * 4, 0, kCpolSc1);
+    }
+  };
+  f32x4 rec_o[kCh];
+  if (wave < 2 * gq) load_records(wave, lane >> 5, rec_o);
   // split weights w_s = l_s 2^(m_s - M) (M the largest m_s of a non-empty
   // split) and their sum, one wave per head, lanes over the splits; kept in
   // LDS (s_part reused: gq * S <= 16 * kMaxSplits = 4,096 weights, then the
@@ -479,30 +523,21 @@ __global__ __launch_bounds__(kThreads) void tq4_decode_kernel(
     if (lane == 0) s_den[h] = den;
   }
   __syncthreads();
-  // o = sum_s w_s o_s / sum_s w_s.  A wave task is (head, half of the dims);
-  // lane (c, k) = (lane % 32, lane / 32) sums dims 128 half + 4 c .. + 3 over
-  // the splits k, k + 2, ..., kCh independent 16-byte record loads at a time
-  constexpr int kCh = 32;
+  // o = sum_s w_s o_s / sum_s w_s
   for (int task = wave; task < 2 * gq; task += kWaves) {
     const int h = task >> 1, k = lane >> 5;
     const int d0 = (kD / 2) * (task & 1) + 4 * (lane & 31);
-    const auto rs = head_records(ws + ((size_t)b * Hq + h0 + h) * max_splits * (kD + 4), max_splits);
     float4 acc = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     for (int s0 = k; s0 < S; s0 += 2 * kCh) {
-      f32x4 o[kCh];
-#pragma unroll
-      for (int i = 0; i < kCh; ++i) {  // past the end: a valid record, weight 0
-        const int s = min(s0 + 2 * i, S - 1);
-        o[i] = __builtin_amdgcn_raw_buffer_load_b128(rs, (s * (kD + 4) + d0) * 4, 0, kCpolSc1);
-      }
+      if (task != wave || s0 != k) load_records(task, s0, rec_o);
 #pragma unroll
       for (int i = 0; i < kCh; ++i) {
         const int s = s0 + 2 * i;
         const float w = s < S ? s_w[h * S + s] : 0.0f;
-        acc.x = fmaf(w, o[i].x, acc.x);
-        acc.y = fmaf(w, o[i].y, acc.y);
-        acc.z = fmaf(w, o[i].z, acc.z);
-        acc.w = fmaf(w, o[i].w, acc.w);
+        acc.x = fmaf(w, rec_o[i].x, acc.x);
+        acc.y = fmaf(w, rec_o[i].y, acc.y);
+        acc.z = fmaf(w, rec_o[i].z, acc.z);
+        acc.w = fmaf(w, rec_o[i].w, acc.w);
       }
     }
     acc.x += __shfl_xor(acc.x, 32);
@@ -519,10 +554,25 @@ __global__ __launch_bounds__(kThreads) void tq4_decode_kernel(
     }
   }
   __syncthreads();
-  fwht_rows(s_x, gq);
-  for (int o = tid; o < gq * kD; o += kThreads) {
-    const int h = o / kD, d = o % kD;
-    out[((size_t)b * Hq + h0 + h) * kD + d] = __float2half(v_signs[d] * s_x[o] * 0.0625f);
+  // rotated back, four heads per wave
+  for (int hq0 = 4 * wave; hq0 < gq; hq0 += 4 * kWaves) {
+    const int h = min(hq0 + q4, gq - 1);
+    float e[2][8];
+#pragma unroll
+    for (int hf = 0; hf < 2; ++hf)
+#pragma unroll
+      for (int i = 0; i < 8; ++i) e[hf][i] = s_x[h * kD + 128 * hf + 8 * rl.chunk + i];
+    fwht_row(e, rl);
+    if (hq0 + q4 < gq) {
+#pragma unroll
+      for (int hf = 0; hf < 2; ++hf) {
+        const int d0 = 128 * hf + 8 * rl.chunk;
+        __half* dst = out + ((size_t)b * Hq + h0 + h) * kD + d0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+          dst[i] = __float2half(v_signs[d0 + i] * (rl.sign * e[hf][i]) * 0.0625f);
+      }
+    }
   }
 }
 
