@@ -87,6 +87,7 @@ constexpr int kWaves = 8;         // two waves per SIMD, one block per CU
 constexpr int kParts = 4;         // per-wave partial buffers (waves w and w + 4 merge first)
 constexpr int kThreads = 64 * kWaves;
 constexpr int kRowPos = 32;       // positions per row (two 16-position tiles)
+constexpr int kPitch = kD + 4;    // of a head's partial: 256 values, m, l (16-byte rows)
 constexpr int kMaxCols = 16;      // query heads per KV head: one column block
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kTau = 2.0f;      // lazy-rescale margin, log2 units
@@ -141,7 +142,7 @@ __global__ __launch_bounds__(kThreads) void tq4_decode_kernel(
   __shared__ __attribute__((aligned(65536))) uint32_t s_tab[256 * 64];
   float* const s_x = reinterpret_cast<float*>(s_tab);     // [kMaxCols][kD]
   static_assert(kMaxCols * kD <= 256 * 64, "the rows fit the table's bytes");
-  __shared__ __attribute__((aligned(16))) float s_part[kParts][kMaxCols * (kD + 2)];  // per-wave partials (u, m, l)
+  __shared__ __attribute__((aligned(16))) float s_part[kParts][kMaxCols * kPitch];  // per-wave partials (u, m, l)
   float* const s_q = s_part[0];                           // before the loop: q' [kMaxCols][kD]
   __shared__ h8 s_qop[8][2][64];                         // score B operands (q' high, low)
   __shared__ uint32_t s_ticket;
@@ -401,29 +402,34 @@ __global__ __launch_bounds__(kThreads) void tq4_decode_kernel(
     float* part = s_part[wave & (kParts - 1)];
     if (wave >= kParts && l16 < gq) {
 #pragma unroll
-      for (int j = 0; j < 16; ++j)
+      for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) part[l16 * (kD + 2) + 64 * q4 + 16 * i + j] = acc_v[j][i];
+        for (int j = 0; j < 16; j += 4)
+          *reinterpret_cast<f32x4*>(&part[l16 * kPitch + 64 * q4 + 16 * i + j]) =
+              f32x4{acc_v[j][i], acc_v[j + 1][i], acc_v[j + 2][i], acc_v[j + 3][i]};
       if (q4 == 0) {
-        part[l16 * (kD + 2) + kD] = m_run;
-        part[l16 * (kD + 2) + kD + 1] = lsum;
+        part[l16 * kPitch + kD] = m_run;
+        part[l16 * kPitch + kD + 1] = lsum;
       }
     }
     __syncthreads();
     if (wave < kParts && l16 < gq) {
-      const float mo = part[l16 * (kD + 2) + kD], lo = part[l16 * (kD + 2) + kD + 1];
+      const float mo = part[l16 * kPitch + kD], lo = part[l16 * kPitch + kD + 1];
       const float M = fmaxf(m_run, mo);
       const float f = __builtin_amdgcn_exp2f(m_run - M), fo = __builtin_amdgcn_exp2f(mo - M);
 #pragma unroll
-      for (int j = 0; j < 16; ++j)
+      for (int i = 0; i < 4; ++i)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          float* u = &part[l16 * (kD + 2) + 64 * q4 + 16 * i + j];
-          *u = fmaf(f, acc_v[j][i], fo * *u);
+        for (int j = 0; j < 16; j += 4) {
+          f32x4* p = reinterpret_cast<f32x4*>(&part[l16 * kPitch + 64 * q4 + 16 * i + j]);
+          f32x4 u = *p;
+#pragma unroll
+          for (int x = 0; x < 4; ++x) u[x] = fmaf(f, acc_v[j + x][i], fo * u[x]);
+          *p = u;
         }
       if (q4 == 0) {
-        part[l16 * (kD + 2) + kD] = M;
-        part[l16 * (kD + 2) + kD + 1] = fmaf(f, lsum, fo * lo);
+        part[l16 * kPitch + kD] = M;
+        part[l16 * kPitch + kD + 1] = fmaf(f, lsum, fo * lo);
       }
     }
   }
@@ -433,15 +439,15 @@ __global__ __launch_bounds__(kThreads) void tq4_decode_kernel(
     float mw[kParts], M = kMinit;
 #pragma unroll
     for (int w = 0; w < kParts; ++w) {
-      mw[w] = s_part[w][h * (kD + 2) + kD];
+      mw[w] = s_part[w][h * kPitch + kD];
       M = fmaxf(M, mw[w]);
     }
     float num = 0.0f, den = 0.0f;
 #pragma unroll
     for (int w = 0; w < kParts; ++w) {
       const float f = __builtin_amdgcn_exp2f(mw[w] - M);
-      num = fmaf(f, s_part[w][h * (kD + 2) + d], num);
-      den = fmaf(f, s_part[w][h * (kD + 2) + kD + 1], den);
+      num = fmaf(f, s_part[w][h * kPitch + d], num);
+      den = fmaf(f, s_part[w][h * kPitch + kD + 1], den);
     }
     float* rec = ws + (((size_t)b * Hq + h0 + h) * max_splits + split) * (kD + 4);
     __hip_atomic_store(&rec[d], den > 0.0f ? num / den : 0.0f, __ATOMIC_RELAXED,
@@ -494,7 +500,7 @@ __global__ __launch_bounds__(kThreads) void tq4_decode_kernel(
   // gq sums)
   float* s_w = s_part[0];                   // [gq][S]
   float* s_den = s_part[0] + kMaxCols * kMaxSplits;  // [gq]
-  static_assert(kMaxCols * kMaxSplits + kMaxCols <= kMaxCols * (kD + 2), "weights fit");
+  static_assert(kMaxCols * kMaxSplits + kMaxCols <= kMaxCols * kPitch, "weights fit");
   for (int h = wave; h < gq; h += kWaves) {
     const auto rs = head_records(ws + ((size_t)b * Hq + h0 + h) * max_splits * (kD + 4), max_splits);
     float mv[kMaxSplits / 64], lv[kMaxSplits / 64];
