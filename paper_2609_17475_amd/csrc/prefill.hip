@@ -936,26 +936,35 @@ __global__ __launch_bounds__(64 * SW * TW) void prefill_combine_kernel(
 // How a call's work is laid over the chip: n_blk blocks per KV head share the
 // head's `tiles` key tiles (over all its row blocks) evenly, or n_blk = 0: one
 // block per row block.  A block fills a CU, so row blocks that do not fill the
-// chip, or leave its last turn nearly empty, cost as much as if they did.  An
-// even share costs a query load, a pipeline fill and a state to store for each
-// row block that it touches (kPartCost tiles) and the combine's launch and
-// reads (kCombineCost tiles), in tiles of about 3.3 us at head_dim 128, 2.1 us
-// at 64 and 256 (fitted to both layouts at 50 shapes of 20..2,048 rows over
-// 0..20,000 positions); a chunk without a prefix has tiles of 2.5 us, so there
-// both count twice.  Measured, split against one block per row block:
-// 256 rows over 196,608 (24/4 heads, 256) 2.50 against 13.1 ms; 1,000 over
-// 7,000 (32/8, 128) 218 against 392 us; 100 over 20,000 (4/1, 128) 37 against
-// 1,010 us; and where the rule keeps row blocks whole: 2,048 over none (32/8,
-// 128) 100 against 81 us, 1,000 over none 47 against 44 us.
+// chip, or leave its last turn nearly empty, cost as much as if they did.
+// Shares of one tile pay while half the chip takes them, otherwise two tiles
+// and more.  Against whole row blocks an even share costs, in tiles (of about
+// 3.3 us at head_dim 128, 2.1 us at 64 and 256): the combine's launch
+// (kCombineCost); a query load, a pipeline fill and a state to store for each
+// further row block that it touches (kPartCost); and the states' traffic, in
+// proportion to the blocks (kFullCost when they fill the chip).  (The combine's
+cost includes the caller's second launch and workspace, which bound a call
+from Python to ~17 us.)  Without a
+// prefix a tile takes 2.5 us and the shares are short: there the first two
+// count twice as much and more, and shares have four tiles at least.
+// Fitted to both layouts at 110 shapes of 16..2,048 rows over 0..20,000
+// positions.  Measured, even shares against whole row blocks: 256 rows over
+// 196,608 (24/4 heads, 256) 2.50 against 13.1 ms; 1,000 over 7,000 (32/8, 128)
+// 218 against 392 us; 100 over 20,000 (4/1, 128) 37 against 1,010 us; 72 over
+// 162 (4/1, 128) 17 against 23 us; and where row blocks stay whole: 16 over 162
+// (4/1, 128) 18.1 against 17.4 us, 2,048 over none (32/8, 128) 100 against 81.
 struct PrefillPlan {
   int64_t n_rb = 0, tiles = 0;
   int n_blk = 0;
 };
 template <int D>
-constexpr int64_t kPartCost = D == 128 ? 1 : D == 64 ? 2 : 5;
+constexpr double kCombineCost = D == 128 ? 3 : D == 64 ? 5.5 : 4;
 template <int D>
-constexpr int64_t kCombineCost = D == 128 ? 3 : D == 64 ? 5 : 8;
-constexpr int64_t kMinShare = 4;   // tiles per block of a split call, at least
+constexpr double kPartCost = D == 128 ? 1 : D == 64 ? 2 : 5;
+template <int D>
+constexpr double kFullCost = D == 256 ? 10 : 6;
+template <int D>
+constexpr double kBareCost = D == 128 ? 5 : D == 64 ? 9 : 18;  // kCombineCost without a prefix, half
 constexpr int64_t kMaxTurns = 16;  // row blocks per CU above which the last turn hardly counts
 
 template <int D>
@@ -974,15 +983,19 @@ PrefillPlan plan_t(const jf_kv_layout& L, int32_t T, int32_t Hq, int32_t prefix_
     p.tiles += rbt.tiles();
     if (rb % per_head == per_head - 1 || rb == p.n_rb - 1) whole += rbt.tiles();
   }
-  const int64_t n_blk = std::min(per_head, std::max<int64_t>(1, p.tiles / kMinShare));
+  const int64_t n_blk =
+      n_pre ? std::max(std::min(p.tiles, per_head / 2), std::min(p.tiles / 2, per_head))
+            : std::min(p.tiles / 4, per_head);
+  if (n_blk <= 1) return p;
   const int64_t share = (p.tiles + n_blk - 1) / n_blk;
   // row blocks that a share touches: most where they are shortest, at the start
   int64_t touched = 1, at = 0;
   rbt = jfkv::RowBlockTiles(kRows, T, gq, n_pre, KT);
   for (; touched <= p.n_rb && (at += rbt.tiles()) < share; rbt.next()) ++touched;
-  const int64_t cost = (kPartCost<D> * (touched + 1) + kCombineCost<D>) * (n_pre ? 1 : 2);
-  if (n_blk > 1 && share + cost < whole &&
-      (n_blk + 1) * p.tiles <= INT32_MAX)  // (the kernels' products of shares and tiles)
+  const double more = kPartCost<D> * (touched - 1);
+  const double cost = n_pre ? kCombineCost<D> + more + kFullCost<D> * n_blk / per_head
+                            : 2 * (kBareCost<D> + more);
+  if (share + cost < whole && (n_blk + 1) * p.tiles <= INT32_MAX)  // (the kernels' products)
     p.n_blk = (int)n_blk;
   return p;
 }

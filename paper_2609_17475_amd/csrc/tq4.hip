@@ -411,8 +411,8 @@ hipError_t launch_tq4_encode(const jf_kv_layout& L, void* words, void* norms, co
   // 20,000 rows)
   constexpr int kPerBlock = kWavesPerBlock * kBatch;
   constexpr int64_t kBlocksPerCu = 8;
-  const int64_t blocks = std::min<int64_t>((n_vec + kPerBlock - 1) / kPerBlock,
-                                           kBlocksPerCu * num_cus());
+  const int64_t need = (n_vec + kPerBlock - 1) / kPerBlock;
+  const int64_t blocks = need <= 64 * kBlocksPerCu ? need : std::min(need, kBlocksPerCu * num_cus());
   if (n_vec > 0x7fffffffLL) return hipErrorInvalidValue;
   hipLaunchKernelGGL(tq4_encode_kernel, dim3((unsigned)blocks), dim3(64 * kWavesPerBlock), 0,
                      stream, static_cast<uint32_t*>(words), static_cast<__half*>(norms),

@@ -418,6 +418,17 @@ def jf_prefill_workspace_bytes(lay: Layout, T: int, num_q_heads: int, prefix_len
     return n.value
 
 
+def _scratch(nbytes: int, device):
+    """Bytes from the caching allocator for work on the current stream, or None."""
+    import torch
+    if torch.cuda.is_current_stream_capturing():
+        return None
+    try:
+        return torch.empty(nbytes, dtype=torch.uint8, device=device)
+    except torch.OutOfMemoryError:
+        return None
+
+
 def _prefill_call(head, tail, nbytes: int, device, stream):
     """One prefill launch: head and tail are the call's arguments around the
     workspace.  The scratch of a split call comes from torch's caching
@@ -428,14 +439,13 @@ def _prefill_call(head, tail, nbytes: int, device, stream):
     import torch
     ws = None
     if nbytes and device.index == torch.cuda.current_device():
-        if stream is not None and not isinstance(stream, torch.cuda.Stream):
-            stream = torch.cuda.ExternalStream(stream.cuda_stream)
-        with torch.cuda.stream(stream):  # (None: the current stream)
-            if not torch.cuda.is_current_stream_capturing():
-                try:
-                    ws = torch.empty(nbytes, dtype=torch.uint8, device=device)
-                except torch.OutOfMemoryError:
-                    pass
+        if stream is None:
+            ws = _scratch(nbytes, device)
+        else:
+            if not isinstance(stream, torch.cuda.Stream):
+                stream = torch.cuda.ExternalStream(stream.cuda_stream)
+            with torch.cuda.stream(stream):
+                ws = _scratch(nbytes, device)
     if ws is None:
         _check(lib.jf_prefill_attn_q4(*head, *tail))
     else:
@@ -451,7 +461,7 @@ def _prefill_args(pool: KVPool, q, k_chunk, v_chunk, block_table, prefix_len, so
             _ptr(block_table), block_table.shape[-1], int(prefix_len), float(softmax_scale))
     tail = (_ptr(out), _stream(stream))
     nbytes = 0
-    if prefix_len + T > 256:  # (below, a split never pays: at most eight tiles per row block)
+    if T + prefix_len > (64 if prefix_len else 256):  # (a split never pays below)
         try:
             nbytes = jf_prefill_workspace_bytes(lay, T, Hq, int(prefix_len))
         except JfError:  # sizes the call itself refuses, with its own message

@@ -6,9 +6,9 @@ partial, waves without rows, and a page outside the pool.
 
 Both calls run the same products per tile; only the fp32 sums over tiles are
 taken in another order (and relative to another running maximum, so p is
-rounded to fp16 at another scale, at most 2^-11 relative each): they agree to
-the tolerance both hold against the oracle, 2e-3 + 2^-11 |o| elementwise and
-1e-3 in relative L2."""
+rounded to fp16 at another scale, at most 2^-11 relative each).  Both hold the
+oracle's tolerance of test_gpu_prefill, 2e-3 + 2^-11 |o| elementwise and 1e-3
+in relative L2, so they are at most twice that apart."""
 import ctypes
 
 import numpy as np
@@ -80,7 +80,8 @@ def test_split_prefill_matches_oracle_and_whole_row_blocks(P, hkv, hq, d, G, p0,
     torch.cuda.synchronize()
     assert torch.equal(split, bound)
     tol = dict(atol=2e-3, rel_elem=2.0 ** -11, rel_l2=1e-3)
-    check_tol(split.cpu().numpy(), whole.double().cpu().numpy(), what="split against whole", **tol)
+    check_tol(split.cpu().numpy(), whole.double().cpu().numpy(), what="split against whole",
+              **{k: 2 * v for k, v in tol.items()})
     if bad is not None:  # (the oracle takes no page outside the pool)
         return
     ref = oracle.prefill(case.host, q, kc, vc, table, p0, scale)
