@@ -943,8 +943,8 @@ __global__ __launch_bounds__(64 * SW * TW) void prefill_combine_kernel(
 // (kCombineCost); a query load, a pipeline fill and a state to store for each
 // further row block that it touches (kPartCost); and the states' traffic, in
 // proportion to the blocks (kFullCost when they fill the chip).  (The combine's
-cost includes the caller's second launch and workspace, which bound a call
-from Python to ~17 us.)  Without a
+// cost includes the caller's second launch and workspace, which bound a call
+// from Python to ~17 us.)  Without a
 // prefix a tile takes 2.5 us and the shares are short: there the first two
 // count twice as much and more, and shares have four tiles at least.
 // Fitted to both layouts at 110 shapes of 16..2,048 rows over 0..20,000
