@@ -452,31 +452,28 @@ def _prefill_call(head, tail, nbytes: int, device, stream):
         _check(lib.jf_prefill_attn_q4_ws(*head, ws.data_ptr(), nbytes, *tail))
 
 
-def _prefill_args(pool: KVPool, q, k_chunk, v_chunk, block_table, prefix_len, softmax_scale, out,
-                  stream):
-    _check_prefill_args(pool, q, k_chunk, v_chunk, block_table, out)
-    lay, ptrs = pool.layout, pool.ptrs()
-    T, Hq, _ = q.shape
-    head = (ctypes.byref(lay), ctypes.byref(ptrs), _ptr(q), _ptr(k_chunk), _ptr(v_chunk), T, Hq,
-            _ptr(block_table), block_table.shape[-1], int(prefix_len), float(softmax_scale))
-    tail = (_ptr(out), _stream(stream))
-    nbytes = 0
-    if T + prefix_len > (64 if prefix_len else 256):  # (a split never pays below)
-        try:
-            nbytes = jf_prefill_workspace_bytes(lay, T, Hq, int(prefix_len))
-        except JfError:  # sizes the call itself refuses, with its own message
-            pass
-    return head, tail, nbytes, (lay, ptrs)
+def _prefill_scratch_bytes(lay: Layout, T: int, Hq: int, prefix_len: int) -> int:
+    if T + prefix_len <= (64 if prefix_len else 256):
+        return 0  # (a split never pays)
+    try:
+        return jf_prefill_workspace_bytes(lay, T, Hq, prefix_len)
+    except JfError:  # sizes the call itself refuses, with its own message
+        return 0
 
 
 def jf_prefill_attn_q4(pool: KVPool, q, k_chunk, v_chunk, block_table, prefix_len: int,
                        softmax_scale: float, out, stream=None):
-    head, tail, nbytes, _ = _prefill_args(pool, q, k_chunk, v_chunk, block_table, prefix_len,
-                                          softmax_scale, out, stream)
+    _check_prefill_args(pool, q, k_chunk, v_chunk, block_table, out)
+    lay = pool.layout
+    T, Hq, _ = q.shape
+    ptrs = pool.ptrs()
+    head = (ctypes.byref(lay), ctypes.byref(ptrs), _ptr(q), _ptr(k_chunk), _ptr(v_chunk), T, Hq,
+            _ptr(block_table), block_table.shape[-1], int(prefix_len), float(softmax_scale))
+    nbytes = _prefill_scratch_bytes(lay, T, Hq, int(prefix_len))
     if nbytes:
-        _prefill_call(head, tail, nbytes, q.device, stream)
+        _prefill_call(head, (_ptr(out), _stream(stream)), nbytes, q.device, stream)
     else:
-        _check(lib.jf_prefill_attn_q4(*head, *tail))
+        _check(lib.jf_prefill_attn_q4(*head, _ptr(out), _stream(stream)))
 
 
 # ------------------------------------------------------------ pre-bound calls
@@ -560,10 +557,14 @@ def bind_prefill(pool: KVPool, q, k_chunk, v_chunk, block_table, prefix_len, sof
                  stream=None) -> BoundCall:
     import torch
     stream = torch.cuda.current_stream() if stream is None else stream
-    head, tail, nbytes, own = _prefill_args(pool, q, k_chunk, v_chunk, block_table, prefix_len,
-                                            softmax_scale, out, stream)
-    return BoundPrefill(head, tail, nbytes, q.device, stream,
-                        (*own, pool, q, k_chunk, v_chunk, block_table, out))
+    _check_prefill_args(pool, q, k_chunk, v_chunk, block_table, out)
+    lay, ptrs = pool.layout, pool.ptrs()
+    T, Hq, _ = q.shape
+    head = (ctypes.byref(lay), ctypes.byref(ptrs), _ptr(q), _ptr(k_chunk), _ptr(v_chunk), T, Hq,
+            _ptr(block_table), block_table.shape[-1], int(prefix_len), float(softmax_scale))
+    return BoundPrefill(head, (_ptr(out), _stream(stream)),
+                        _prefill_scratch_bytes(lay, T, Hq, int(prefix_len)), q.device, stream,
+                        (lay, ptrs, pool, q, k_chunk, v_chunk, block_table, out))
 
 
 def jf_reconstruct_q4(pool: KVPool, block_table, n_pos: int, kv0: int, num_heads: int, k_out,
