@@ -84,16 +84,23 @@ __device__ __forceinline__ float add_squares(uint32_t w, float q) {
   return q;
 }
 
-// Sign bits of signs[element] * by for a lane's elements, as bits of fp16 pairs.
-__device__ __forceinline__ void sign_bits(uint32_t (&sx)[2][4], const float* signs, int chunk,
-                                          float by) {
+// a * b in float32, with +0 for either zero.  (Written out: the compiler makes
+// an fma that is then rounded to fp16 a mixed-precision one, which rounds once.)
+__device__ __forceinline__ float mul_pz(float a, float b) {
+  float r;
+  asm("v_fma_f32 %0, %1, %2, 0" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+
+// Sign bits of a lane's elements' signs, as bits of fp16 pairs.
+__device__ __forceinline__ void sign_bits(uint32_t (&sx)[2][4], const float* signs, int chunk) {
 #pragma unroll
   for (int h = 0; h < 2; ++h)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const float* sp = signs + 128 * h + 8 * chunk + 2 * i;
-      sx[h][i] = (__builtin_bit_cast(uint32_t, sp[0] * by) >> 31 << 15) |
-                 (__builtin_bit_cast(uint32_t, sp[1] * by) & 0x80000000u);
+      sx[h][i] = (__builtin_bit_cast(uint32_t, sp[0]) >> 31 << 15) |
+                 (__builtin_bit_cast(uint32_t, sp[1]) & 0x80000000u);
     }
 }
 
@@ -151,7 +158,7 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void tq4_encode_kernel(
   // (the table is aligned to its size: an entry's address is base | bits | copy)
   const uint32_t copy = (uint32_t)(uintptr_t)&bucket[0][lane & (kCopies - 1)];
   uint32_t sx[2][4];  // the signs of the lane's elements, as bits of fp16 pairs
-  sign_bits(sx, signs, rl.chunk, 1.0f);
+  sign_bits(sx, signs, rl.chunk);
 
   // wave-uniform: the batches wave, wave + W, ... (the host bounds n_vec by
   // INT32_MAX)
@@ -342,10 +349,8 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void tq4_reconstruct_kernel(
       rho[v] = __half2float(norms[vec]);
     }
   }
-  // signs of the lane's elements times the transform's, as bits of fp16 pairs
-  const float* signs = is_v ? v_signs : k_signs;
   uint32_t sx[2][4];
-  sign_bits(sx, signs, rl.chunk, rl.sign);
+  sign_bits(sx, is_v ? v_signs : k_signs, rl.chunk);
   __syncthreads();
 #pragma unroll
   for (int v = 0; v < kRecBatches; ++v) {
@@ -362,13 +367,16 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void tq4_reconstruct_kernel(
         e[h][i + 1] = c0 - c1;
       }
     fwht_from1(e, rl);
-    const float f = rho[v] * 0.0625f;
+    // the lane holds rl.sign times the transform, but sums that cancel are +0
+    // in every lane: mul_pz keeps them so, and a zero's sign is then that of
+    // its element's sign, whatever the lane
+    const float f = rl.sign * rho[v] * 0.0625f;
     u32x4 o[2];
 #pragma unroll
     for (int h = 0; h < 2; ++h)
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        o[h][i] = ok[v] ? __builtin_bit_cast(uint32_t, __floats2half2_rn(e[h][2 * i] * f, e[h][2 * i + 1] * f)) ^ sx[h][i]
+        o[h][i] = ok[v] ? __builtin_bit_cast(uint32_t, __floats2half2_rn(mul_pz(e[h][2 * i], f), mul_pz(e[h][2 * i + 1], f))) ^ sx[h][i]
                         : 0u;
     if (t < n) {
       u32x4* dst = reinterpret_cast<u32x4*>(out + ((int64_t)j * n + t) * (kD / 4)) + rl.chunk;

@@ -576,7 +576,8 @@ __global__ __launch_bounds__(kThreads) void tq4_decode_kernel(
         __half* dst = out + ((size_t)b * Hq + h0 + h) * kD + d0;
 #pragma unroll
         for (int i = 0; i < 8; ++i)
-          dst[i] = __float2half(v_signs[d0 + i] * (rl.sign * e[hf][i]) * 0.0625f);
+          // (the + 0: sums that cancel are +0 whatever the lane's sign)
+          dst[i] = __float2half(v_signs[d0 + i] * fmaf(rl.sign, e[hf][i], 0.0f) * 0.0625f);
       }
     }
   }

@@ -4,10 +4,15 @@ itself), a last batch that is not full, more batches than the grid's waves
 take at once, and pages shorter than the run of positions a wave rebuilds.
 Oracle, bounds and poison checks are those of test_gpu_tq4 and
 test_gpu_reconstruct."""
+import numpy as np
 import pytest
+import torch
 
 pytestmark = pytest.mark.gpu
 
+from gpu_cases import log  # noqa: E402
+from paper_2609_17475_amd import jfkv  # noqa: E402
+from test_gpu_tq4_decode import Case  # noqa: E402
 from test_gpu_reconstruct import test_tq4_reconstruct_matches_oracle as check_reconstruct  # noqa: E402
 from test_gpu_tq4 import run_case  # noqa: E402
 
@@ -29,3 +34,25 @@ def test_encode_batches(P, hkv, lens, starts, NP):
 ])
 def test_reconstruct_short_pages(P, hkv, L, n, kv0, g):
     check_reconstruct(P, hkv, L, n, kv0, g)
+
+
+@pytest.mark.parametrize("index", [1, 14])  # a negative and a positive centroid
+def test_cancelled_sums_are_positive_zeros(index):
+    """A vector of one centroid transforms to 256 c in element 0 and sums that
+    cancel elsewhere: +0 in fp32 (x - x), whatever lane holds them, so that the
+    fp16 result there is a zero with the sign of its element's sign (to the bit)."""
+    log("tq4 cancelled sums, index %d" % index)
+    P, L = 64, 70
+    c = Case(P, 1, (L,), seed=index)
+    for pool in (c.k_pool, c.v_pool):
+        pool.words.fill_(index * 0x11111111 - (1 << 32 if index > 7 else 0))
+        pool.norms.fill_(1.0)
+    k, v = (torch.full((1, L, 256), float("nan"), dtype=torch.float16, device="cuda") for _ in range(2))
+    jfkv.jf_tq4_reconstruct(c.k_pool, c.v_pool, c.dev["sk"], c.dev["sv"], c.dev["c"],
+                            torch.from_numpy(c.tables[0]).to("cuda"), L, 0, 1, k, v)
+    o = c.gpu(np.zeros((1, 4, 256), np.float16), lens=[1])
+    for what, got, s in (("K", k, c.sk), ("V", v, c.sv), ("decode", torch.from_numpy(o), c.sv)):
+        got = got.cpu().numpy().reshape(-1, 256)
+        assert np.all(np.abs(got[:, 0] - s[0] * 16 * np.float64(c.c[index])) <= 2e-3 * 16 * abs(c.c[index]))
+        assert not np.any(got[:, 1:]), what
+        assert np.array_equal(np.signbit(got[:, 1:]), np.broadcast_to(s[1:] < 0, got[:, 1:].shape)), what
