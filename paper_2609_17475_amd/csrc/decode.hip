@@ -83,6 +83,7 @@ constexpr float kMinit = -1e30f;
 constexpr int kMaxThreads = 512;    // a block: one split, one block per CU
 constexpr int kRowPos = 32;         // positions per row: two 16-position MFMA tiles
 constexpr int kXcds = 8;            // XCDs of the chip (block placement only)
+constexpr int kCuLds = 163840;       // LDS bytes of a CU
 constexpr int kRingBudget = 162816; // LDS bytes of a block's rings (a CU's LDS less 1 KiB)
 // Waves per block: two per SIMD where the LDS rings fit (d <= 128), so one
 // wave computes while the other waits on its page loads; the waves meet at a
@@ -518,7 +519,11 @@ __global__ __launch_bounds__(kMaxThreads, RING == kPairStages && D == 128 ? 4 : 
   static_assert(kChunk * D + 2 * kChunk <= kStages * kStageBytes / 4, "merge fits a ring");
 
   __shared__ __attribute__((aligned(16))) uint8_t smem[kWaves][kStages][kStageBytes];
-  __shared__ uint32_t s_ticket;
+  // two blocks of two-stage rings share a CU only if nothing lies beside the
+  // rings: with 32-dim groups they take all of its LDS (the ticket is kept in
+  // a ring, idle by then)
+  static_assert(RING != kPairStages || D < 128 || 2 * kWaves * kStages * kStageBytes <= kCuLds,
+                "two blocks per CU");
 
   // Block -> (split, KV head, head chunk).  One head chunk: x = split,
   // y = KV head.  Several chunks read the same pages, so their blocks are
@@ -1235,10 +1240,11 @@ __global__ __launch_bounds__(kMaxThreads, RING == kPairStages && D == 128 ? 4 : 
   wait_vm<0>();     // this thread's records are stored
   __syncthreads();  // ... and every thread's; the merge buffers are free
   uint32_t* ticket = tickets + ((size_t)b * Hkv + kv) * n_hchunks + hc;
+  uint32_t* const s_ticket = reinterpret_cast<uint32_t*>(smem[0][0]);
   if (tid == 0)
-    s_ticket = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    *s_ticket = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   __syncthreads();
-  if (s_ticket != (uint32_t)(S - 1)) return;
+  if (*s_ticket != (uint32_t)(S - 1)) return;
   if (tid == 0) __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   combine_splits<D, (kChunk < kWaves ? kWaves / kChunk : 1), kWaves>(ws, out, b, Hq, sq, h0, nh,
                                                                         max_splits, S);
@@ -1271,10 +1277,14 @@ hipError_t launch_cs(const jf_kv_layout& L, const jf_kv_pool_ptrs& pool, const v
   // fixed costs pass under the other's page loop; longer ones are bound by HBM
   // and stream better with three stages per wave (at head_dim 256, with half
   // the waves, two blocks always win).  The results are the same to the bit.
-  // Fused step, 32/8 heads, d = 128, three stages against pairs: 2 x 20K
-  // positions 25.8 / 21.1 us, 2 x 80K 47.5 / 44.5, 8 of 9K..30K 88.7 / 62.3,
-  // 2 x 130K 64.9 / 65.3, 196K + 131K 74.4 / 76.5; 24/4 heads, d = 256: 2 x 20K
-  // 37.1 / 28.9, 2 x 130K 118 / 98.  (Here at d = 64 two blocks fit anyway.)
+  // Fused step, three stages against pairs.  32/8 heads, d = 128, 64-dim
+  // groups: 2 x 20K positions 25.8 / 21.1 us, 2 x 80K 47.5 / 44.5, 8 of
+  // 9K..30K 88.7 / 62.3, 2 x 130K 64.9 / 65.3, 196K + 131K 74.4 / 76.5; 32-dim
+  // groups: 2 x 20K 25.9 / 21.4, 8 of 9K..30K 96.2 / 65.6, 2 x 110K 59.5 /
+  // 58.7, 2 x 131K 69.8 / 71.0, 4 of 60K..131K 107 / 101.  d = 256: 24/4 heads,
+  // 64-dim groups, 2 x 20K 37.1 / 28.9, 2 x 130K 118 / 98; 16/4 heads, 32-dim
+  // groups, 2 x 20K 39.5 / 29.0, 2 x 130K 87.5 / 77.1.  (At d = 64 two blocks
+  // of three stages fit anyway.)
   constexpr bool kPairs = CS == 1 && D >= 128;
   constexpr int64_t kPairPositions = 4096;
   const bool pair =
