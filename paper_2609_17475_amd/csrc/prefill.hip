@@ -937,34 +937,36 @@ __global__ __launch_bounds__(64 * SW * TW) void prefill_combine_kernel(
 // head's `tiles` key tiles (over all its row blocks) evenly, or n_blk = 0: one
 // block per row block.  A block fills a CU, so row blocks that do not fill the
 // chip, or leave its last turn nearly empty, cost as much as if they did.
+// Row blocks are started in turn, later ones have more tiles, and a CU takes
+// the next when it is done, so its chain is row blocks i, i + CUs, ...; the
+// longest chain is the time of whole row blocks.
 // Shares of one tile pay while half the chip takes them, otherwise two tiles
-// and more.  Against whole row blocks an even share costs, in tiles (of about
-// 3.3 us at head_dim 128, 2.1 us at 64 and 256): the combine's launch
-// (kCombineCost); a query load, a pipeline fill and a state to store for each
-// further row block that it touches (kPartCost); and the states' traffic, in
-// proportion to the blocks (kFullCost when they fill the chip).  (The combine's
-// cost includes the caller's second launch and workspace, which bound a call
-// from Python to ~17 us.)  Without a
-// prefix a tile takes 2.5 us and the shares are short: there the first two
-// count twice as much and more, and shares have four tiles at least.
-// Fitted to both layouts at 110 shapes of 16..2,048 rows over 0..20,000
-// positions.  Measured, even shares against whole row blocks: 256 rows over
-// 196,608 (24/4 heads, 256) 2.50 against 13.1 ms; 1,000 over 7,000 (32/8, 128)
-// 218 against 392 us; 100 over 20,000 (4/1, 128) 37 against 1,010 us; 72 over
-// 162 (4/1, 128) 17 against 23 us; and where row blocks stay whole: 16 over 162
-// (4/1, 128) 18.1 against 17.4 us, 2,048 over none (32/8, 128) 100 against 81.
+// and more (without a prefix, where tiles are shorter, four).  Against whole
+// row blocks an even share costs, in tiles (SplitCost): the combine's launch;
+// a query load, a pipeline fill and a state to store for each further row
+// block that it touches; and the states' traffic, in proportion to the blocks.
+// Fitted at 980 shapes of 16..8,192 rows, half of them without a prefix, the
+// others over 20..200,000 positions, at 64..8 heads of 64, 128 and 256 dims, of
+// both layouts each (a tile takes 3.0, 1.8 and 2.1 us at head_dim 128, 64 and
+// 256 with a prefix, 2.3, 1.3 and 1.4 without): the rule's choices cost 0.05 %
+// more than the faster layout of each shape, 5 % at most above 30 us.
+// Measured, even shares against whole row blocks: 256 rows over 196,608 (24/4
+// heads, 256) 2.50 against 13.1 ms; 1,000 over 7,000 (32/8, 128) 218 against
+// 392 us; 100 over 20,000 (4/1, 128) 37 against 1,010 us; 72 over 162 (4/1,
+// 128) 17 against 23 us; and where row blocks stay whole: 16 over 162 (4/1,
+// 128) 18.1 against 17.4 us; without a prefix, 4,096 of 32/8 heads, 128, 260
+// against 230, 2,509 of 64/8 256 against 183, 5,981 of 16/2, 64, 214 against 174.
 struct PrefillPlan {
   int64_t n_rb = 0, tiles = 0;
   int n_blk = 0;
 };
-template <int D>
-constexpr double kCombineCost = D == 128 ? 3 : D == 64 ? 5.5 : 4;
-template <int D>
-constexpr double kPartCost = D == 128 ? 1 : D == 64 ? 2 : 5;
-template <int D>
-constexpr double kFullCost = D == 256 ? 10 : 6;
-template <int D>
-constexpr double kBareCost = D == 128 ? 5 : D == 64 ? 9 : 18;  // kCombineCost without a prefix, half
+struct SplitCost {
+  double combine, part, full;  // per call, per further row block touched, of states when they fill the chip
+};
+template <int D, bool PRE>
+constexpr SplitCost kSplitCost = D == 128 ? SplitCost{1, PRE ? 3 : 3.3, PRE ? 5 : 5.5}
+                                 : D == 64 ? (PRE ? SplitCost{4, 3, 2} : SplitCost{1, 4, 6})
+                                           : (PRE ? SplitCost{2, 8, 5.5} : SplitCost{0, 6, 5});
 constexpr int64_t kMaxTurns = 16;  // row blocks per CU above which the last turn hardly counts
 
 template <int D>
@@ -977,12 +979,16 @@ PrefillPlan plan_t(const jf_kv_layout& L, int32_t T, int32_t Hq, int32_t prefix_
   p.n_rb = ((int64_t)T * gq + kRows - 1) / kRows;
   const int64_t per_head = std::max(1, jfkv::num_cus() / L.num_kv_heads);
   if (p.n_rb > kMaxTurns * per_head) return p;
-  int64_t whole = 0;  // tiles of the longest chain of row blocks on one CU
+  // tiles of the two longest chains of row blocks on one CU: the last of those
+  // without and of those with a row block in the last turn
+  int64_t chain[2] = {0, 0};
   jfkv::RowBlockTiles rbt(kRows, T, gq, n_pre, KT);
   for (int64_t rb = 0; rb < p.n_rb; ++rb, rbt.next()) {
     p.tiles += rbt.tiles();
-    if (rb % per_head == per_head - 1 || rb == p.n_rb - 1) whole += rbt.tiles();
+    if (rb % per_head == per_head - 1) chain[0] += rbt.tiles();
+    if (rb % per_head == (p.n_rb - 1) % per_head) chain[1] += rbt.tiles();
   }
+  const int64_t whole = std::max(chain[0], chain[1]);
   const int64_t n_blk =
       n_pre ? std::max(std::min(p.tiles, per_head / 2), std::min(p.tiles / 2, per_head))
             : std::min(p.tiles / 4, per_head);
@@ -992,9 +998,8 @@ PrefillPlan plan_t(const jf_kv_layout& L, int32_t T, int32_t Hq, int32_t prefix_
   int64_t touched = 1, at = 0;
   rbt = jfkv::RowBlockTiles(kRows, T, gq, n_pre, KT);
   for (; touched <= p.n_rb && (at += rbt.tiles()) < share; rbt.next()) ++touched;
-  const double more = kPartCost<D> * (touched - 1);
-  const double cost = n_pre ? kCombineCost<D> + more + kFullCost<D> * n_blk / per_head
-                            : 2 * (kBareCost<D> + more);
+  const SplitCost c = n_pre ? kSplitCost<D, true> : kSplitCost<D, false>;
+  const double cost = c.combine + c.part * (touched - 1) + c.full * n_blk / per_head;
   if (share + cost < whole && (n_blk + 1) * p.tiles <= INT32_MAX)  // (the kernels' products)
     p.n_blk = (int)n_blk;
   return p;
