@@ -967,6 +967,12 @@ template <int D, bool PRE>
 constexpr SplitCost kSplitCost = D == 128 ? SplitCost{1, PRE ? 3 : 3.3, PRE ? 5 : 5.5}
                                  : D == 64 ? (PRE ? SplitCost{4, 3, 2} : SplitCost{1, 4, 6})
                                            : (PRE ? SplitCost{2, 8, 5.5} : SplitCost{0, 6, 5});
+// A split has to gain what its scratch, its second launch and the estimate's own
+// error are worth.  2,048 rows of 32/8 heads (two full turns): over 16,384
+// positions estimated at 2.1 % less, 874 against 897 us; over 32,768 1.1 % less,
+// 1,647 against 1,669; over 65,536 0.6 % less, 3,189 against 3,206; over 131,072
+// 0.3 % less, 6,291 against 6,283.
+constexpr double kWorthwhile = 0.98;
 constexpr int64_t kMaxTurns = 16;  // row blocks per CU above which the last turn hardly counts
 
 template <int D>
@@ -1000,7 +1006,7 @@ PrefillPlan plan_t(const jf_kv_layout& L, int32_t T, int32_t Hq, int32_t prefix_
   for (; touched <= p.n_rb && (at += rbt.tiles()) < share; rbt.next()) ++touched;
   const SplitCost c = n_pre ? kSplitCost<D, true> : kSplitCost<D, false>;
   const double cost = c.combine + c.part * (touched - 1) + c.full * n_blk / per_head;
-  if (share + cost < whole && (n_blk + 1) * p.tiles <= INT32_MAX)  // (the kernels' products)
+  if (share + cost < kWorthwhile * whole && (n_blk + 1) * p.tiles <= INT32_MAX)  // (the kernels' products)
     p.n_blk = (int)n_blk;
   return p;
 }

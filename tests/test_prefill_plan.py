@@ -24,6 +24,10 @@ def splits(hq, hkv, d, group, T, prefix):
     (32, 8, 128, 64, 7917, 0),    # 779.5 / 704.1
     (16, 2, 64, 32, 5981, 0),     # 214.1 / 174.3
     (64, 8, 128, 64, 1792, 53),   # 182.2 / 157.5
+    # two full turns over a long prefix: too little to gain for 71 MB of scratch
+    (32, 8, 128, 64, 2048, 32768),    # 1,647 / 1,669
+    (32, 8, 128, 64, 2048, 65536),    # 3,189 / 3,206
+    (32, 8, 128, 64, 2048, 131072),   # 6,291 / 6,283
 ])
 def test_whole_row_blocks_where_a_split_costs_more(hq, hkv, d, group, T, prefix):
     assert not splits(hq, hkv, d, group, T, prefix)
