@@ -435,7 +435,8 @@ def _prefill_call(head, tail, nbytes: int, device, stream):
     allocator on the call's own stream (so later work on that stream may reuse
     it, and empty_cache() gives it back) and is held for the call only.  Without
     it (none needed, none to be had, or a stream under capture, whose replays
-    would outlive it) the call runs unsplit."""
+    would outlive it) the call runs unsplit: slower, and with the sums in another
+    order, so that the last bits differ from a split call's."""
     import torch
     ws = None
     if nbytes and device.index == torch.cuda.current_device():
@@ -443,7 +444,7 @@ def _prefill_call(head, tail, nbytes: int, device, stream):
             ws = _scratch(nbytes, device)
         else:
             if not isinstance(stream, torch.cuda.Stream):
-                stream = torch.cuda.ExternalStream(stream.cuda_stream)
+                stream = torch.cuda.ExternalStream(stream.cuda_stream or 0)
             with torch.cuda.stream(stream):
                 ws = _scratch(nbytes, device)
     if ws is None:
@@ -461,15 +462,35 @@ def _prefill_scratch_bytes(lay: Layout, T: int, Hq: int, prefix_len: int) -> int
         return 0
 
 
-def jf_prefill_attn_q4(pool: KVPool, q, k_chunk, v_chunk, block_table, prefix_len: int,
-                       softmax_scale: float, out, stream=None):
+def _prefill_args(pool: KVPool, q, k_chunk, v_chunk, block_table, prefix_len, softmax_scale, out,
+                  workspace):
+    """Layout and pool pointers (to be kept for the call), and its arguments up
+    to the workspace (a caller's workspace included)."""
     _check_prefill_args(pool, q, k_chunk, v_chunk, block_table, out)
-    lay = pool.layout
+    lay, ptrs = pool.layout, pool.ptrs()
     T, Hq, _ = q.shape
-    ptrs = pool.ptrs()
     head = (ctypes.byref(lay), ctypes.byref(ptrs), _ptr(q), _ptr(k_chunk), _ptr(v_chunk), T, Hq,
             _ptr(block_table), block_table.shape[-1], int(prefix_len), float(softmax_scale))
-    nbytes = _prefill_scratch_bytes(lay, T, Hq, int(prefix_len))
+    if workspace is not None:
+        _dev_check(workspace, "workspace")
+        head += (_ptr(workspace), workspace.numel() * workspace.element_size())
+    return lay, ptrs, head
+
+
+def jf_prefill_attn_q4(pool: KVPool, q, k_chunk, v_chunk, block_table, prefix_len: int,
+                       softmax_scale: float, out, stream=None, workspace=None):
+    """workspace: a tensor of at least jf_prefill_workspace_bytes() bytes for the
+    split of the call, which the caller keeps while the call (or a graph that
+    holds it) may run; calls that may overlap must not share one.  Without it
+    the scratch comes from torch's allocator (see _prefill_call); with it
+    nothing is allocated, a call under capture is split like any other, and the
+    result's bits don't depend on what memory is free."""
+    lay, ptrs, head = _prefill_args(pool, q, k_chunk, v_chunk, block_table, prefix_len,
+                                    softmax_scale, out, workspace)
+    if workspace is not None:
+        _check(lib.jf_prefill_attn_q4_ws(*head, _ptr(out), _stream(stream)))
+        return
+    nbytes = _prefill_scratch_bytes(lay, q.shape[0], q.shape[1], int(prefix_len))
     if nbytes:
         _prefill_call(head, (_ptr(out), _stream(stream)), nbytes, q.device, stream)
     else:
@@ -544,7 +565,8 @@ def bind_verify(pool: KVPool, q, block_tables, seq_lens, softmax_scale, max_spli
 
 
 class BoundPrefill(BoundCall):
-    """A bound prefill; a split call's workspace is taken for each call."""
+    """A bound prefill without a caller's workspace; a split call's is taken for
+    each call."""
 
     def __init__(self, head, tail, nbytes, device, stream, keep):
         super().__init__(None, (head, tail, nbytes, device, stream), keep)
@@ -554,17 +576,18 @@ class BoundPrefill(BoundCall):
 
 
 def bind_prefill(pool: KVPool, q, k_chunk, v_chunk, block_table, prefix_len, softmax_scale, out,
-                 stream=None) -> BoundCall:
+                 stream=None, workspace=None) -> BoundCall:
+    """workspace as in jf_prefill_attn_q4: the way to capture a split call."""
     import torch
     stream = torch.cuda.current_stream() if stream is None else stream
-    _check_prefill_args(pool, q, k_chunk, v_chunk, block_table, out)
-    lay, ptrs = pool.layout, pool.ptrs()
-    T, Hq, _ = q.shape
-    head = (ctypes.byref(lay), ctypes.byref(ptrs), _ptr(q), _ptr(k_chunk), _ptr(v_chunk), T, Hq,
-            _ptr(block_table), block_table.shape[-1], int(prefix_len), float(softmax_scale))
-    return BoundPrefill(head, (_ptr(out), _stream(stream)),
-                        _prefill_scratch_bytes(lay, T, Hq, int(prefix_len)), q.device, stream,
-                        (lay, ptrs, pool, q, k_chunk, v_chunk, block_table, out))
+    lay, ptrs, head = _prefill_args(pool, q, k_chunk, v_chunk, block_table, prefix_len,
+                                    softmax_scale, out, workspace)
+    tail = (_ptr(out), _stream(stream))
+    keep = (lay, ptrs, pool, q, k_chunk, v_chunk, block_table, out, workspace)
+    if workspace is not None:
+        return BoundCall(lib.jf_prefill_attn_q4_ws, head + tail, keep)
+    return BoundPrefill(head, tail, _prefill_scratch_bytes(lay, q.shape[0], q.shape[1], int(prefix_len)),
+                        q.device, stream, keep)
 
 
 def jf_reconstruct_q4(pool: KVPool, block_table, n_pos: int, kv0: int, num_heads: int, k_out,

@@ -86,3 +86,94 @@ def test_split_prefill_matches_oracle_and_whole_row_blocks(P, hkv, hq, d, G, p0,
         return
     ref = oracle.prefill(case.host, q, kc, vc, table, p0, scale)
     log("  max err %.3e rel L2 %.3e" % check_tol(split.cpu().numpy(), ref, what="split", **tol))
+
+
+def _call(P, hkv, hq, d, G, p0, T):
+    """A split call: its pool and arguments, its workspace's bytes, and what the
+    split call and the call of whole row blocks give."""
+    from gpu_cases import build
+    case = build(P=P, hkv=hkv, d=d, G=G, hq=hq, lens=(p0 + T,), seed=p0 + T)
+    g = torch.Generator(device="cuda").manual_seed(T)
+    q, kc, vc = (torch.randn((T, h, d), generator=g, device="cuda").half() for h in (hq, hkv, hkv))
+    args = (case.gpu, q, kc, vc, torch.from_numpy(case.tables[0]).cuda(), p0, d ** -0.5)
+    nbytes = jfkv.jf_prefill_workspace_bytes(case.lay, T, hq, p0)
+    assert nbytes > 0
+    split, whole = (torch.full_like(q, float("nan")) for _ in range(2))
+    jfkv.jf_prefill_attn_q4(*args, split)
+    lay, ptrs = case.lay, case.gpu.ptrs()
+    jfkv._check(jfkv.lib.jf_prefill_attn_q4(
+        ctypes.byref(lay), ctypes.byref(ptrs), *(a.data_ptr() for a in args[1:4]), T, hq,
+        args[4].data_ptr(), len(args[4]), p0, args[6], whole.data_ptr(),
+        torch.cuda.current_stream().cuda_stream))
+    torch.cuda.synchronize()
+    assert not torch.equal(split, whole)  # (sums in another order: the layouts can be told apart)
+    return args, nbytes, split, whole
+
+
+@pytest.mark.gpu
+def test_callers_workspace_eager_and_captured():
+    """With the caller's workspace a call is split as it is without, eagerly and
+    in a graph, to the bit; a captured call without one keeps row blocks whole."""
+    from gpu_cases import log
+    log("prefill with the caller's workspace, captured")
+    args, nbytes, split, whole = _call(256, 1, 4, 128, 64, 5000, 37)
+    ws = torch.full((nbytes,), 0xA5, dtype=torch.uint8, device="cuda")
+    out = torch.full_like(split, float("nan"))
+    jfkv.jf_prefill_attn_q4(*args, out, workspace=ws)
+    assert torch.equal(out, split)
+    out.fill_(float("nan"))
+    jfkv.bind_prefill(*args, out, workspace=ws)()
+    assert torch.equal(out, split)
+    for short in (ws[:nbytes - 16], ws[8:]):  # too small, misaligned
+        with pytest.raises(jfkv.JfError, match="workspace"):
+            jfkv.jf_prefill_attn_q4(*args, out, workspace=short)
+    with pytest.raises(ValueError, match="workspace"):
+        jfkv.jf_prefill_attn_q4(*args, out, workspace=ws.cpu())
+
+    out2, out3 = torch.full_like(split, float("nan")), torch.full_like(split, float("nan"))
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        jfkv.bind_prefill(*args, out, workspace=ws)()
+        jfkv.jf_prefill_attn_q4(*args, out2)
+        jfkv.bind_prefill(*args, out3)()
+    for _ in range(3):
+        for t in (out, out2, out3):
+            t.fill_(float("nan"))
+        ws.fill_(0xA5)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, split) and torch.equal(out2, whole) and torch.equal(out3, whole)
+        eager = torch.full_like(split, float("nan"))
+        jfkv.jf_prefill_attn_q4(*args, eager)
+        assert torch.equal(eager, split)
+
+
+@pytest.mark.gpu
+def test_other_streams_and_no_memory(monkeypatch):
+    from types import SimpleNamespace
+
+    from gpu_cases import log
+    log("split prefill on other streams, without scratch")
+    args, nbytes, split, whole = _call(64, 2, 8, 128, 32, 3001, 130)
+    side = torch.cuda.Stream()
+    for stream in (side, SimpleNamespace(cuda_stream=side.cuda_stream)):
+        out = torch.full_like(split, float("nan"))
+        torch.cuda.synchronize()
+        jfkv.jf_prefill_attn_q4(*args, out, stream=stream)
+        torch.cuda.synchronize()
+        assert torch.equal(out, split)
+        out.fill_(float("nan"))
+        torch.cuda.synchronize()
+        jfkv.bind_prefill(*args, out, stream=stream)()
+        torch.cuda.synchronize()
+        assert torch.equal(out, split)
+    out = torch.full_like(split, float("nan"))
+
+    def no_memory(*_, **__):
+        raise torch.OutOfMemoryError("no memory")
+
+    monkeypatch.setattr(torch, "empty", no_memory)
+    jfkv.jf_prefill_attn_q4(*args, out)
+    torch.cuda.synchronize()
+    monkeypatch.undo()
+    assert torch.equal(out, whole)
