@@ -83,7 +83,7 @@ constexpr float kMinit = -1e30f;
 constexpr int kMaxThreads = 512;    // a block: one split, one block per CU
 constexpr int kRowPos = 32;         // positions per row: two 16-position MFMA tiles
 constexpr int kXcds = 8;            // XCDs of the chip (block placement only)
-constexpr int kCuLds = 163840;       // LDS bytes of a CU
+constexpr int kCuLds = 163840;      // LDS bytes of a CU
 constexpr int kRingBudget = 162816; // LDS bytes of a block's rings (a CU's LDS less 1 KiB)
 // Waves per block: two per SIMD where the LDS rings fit (d <= 128), so one
 // wave computes while the other waits on its page loads; the waves meet at a

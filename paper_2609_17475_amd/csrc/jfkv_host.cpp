@@ -22,6 +22,7 @@
 #include <vector>
 
 #include "jfkv_internal.h"
+#include "jfkv_prefill_plan.h"
 
 namespace {
 
@@ -88,58 +89,6 @@ bool geometry_supported(const jf_kv_layout& L) {
   bool p_ok = L.page_size % 64 == 0 && L.page_size <= 4096;
   return d_ok && g_ok && p_ok;
 }
-}  // namespace jfkv
-
-namespace {
-
-// Sizes and scale of a prefill call.
-jf_status check_prefill_sizes(const jf_kv_layout* layout, int32_t T, int32_t num_q_heads,
-                              int32_t max_pages, int32_t prefix_len, float softmax_scale) {
-  if (T < 0 || prefix_len < 0 || num_q_heads <= 0 || max_pages < 0)
-    return fail(JF_ERR_INVALID, "negative size");
-  if (num_q_heads % layout->num_kv_heads)
-    return fail(JF_ERR_INVALID, "num_q_heads %d is not a multiple of num_kv_heads %d",
-                num_q_heads, layout->num_kv_heads);
-  if ((int64_t)prefix_len > (int64_t)max_pages * layout->page_size)
-    return fail(JF_ERR_INVALID, "prefix_len %d exceeds max_pages %d * page_size %d",
-                prefix_len, max_pages, layout->page_size);
-  if ((int64_t)prefix_len + T > INT32_MAX)
-    return fail(JF_ERR_INVALID, "prefix_len + T overflows int32");
-  if (!(softmax_scale == softmax_scale) || softmax_scale == INFINITY ||
-      softmax_scale == -INFINITY)
-    return fail(JF_ERR_INVALID, "softmax_scale must be finite");
-  return ok();
-}
-
-}  // namespace
-
-namespace jfkv {
-
-jf_status check_prefill(const jf_kv_layout* layout, const jf_kv_pool_ptrs* pool, const void* q,
-                        const void* k_chunk, const void* v_chunk, int32_t T, int32_t num_q_heads,
-                        const int32_t* block_table, int32_t max_pages, int32_t prefix_len,
-                        float softmax_scale, const void* out) {
-  jf_status st = check_layout(layout);
-  if (st) return st;
-  if ((st = check_pool(pool))) return st;
-  if ((st = check_prefill_sizes(layout, T, num_q_heads, max_pages, prefix_len, softmax_scale)))
-    return st;
-  if (T == 0) return ok();
-  if (!q || !k_chunk || !v_chunk || !out || (prefix_len > 0 && !block_table))
-    return fail(JF_ERR_INVALID, "NULL device pointer");
-  return ok();
-}
-
-jf_status check_prefill_shape(const jf_kv_layout* layout, int32_t T, int32_t num_q_heads,
-                              int32_t prefix_len) {
-  jf_status st = check_layout(layout);
-  if (st) return st;
-  return check_prefill_sizes(layout, T, num_q_heads, INT32_MAX, prefix_len, 0.0f);
-}
-
-jf_status status_invalid(const char* message) { return fail(JF_ERR_INVALID, "%s", message); }
-jf_status status_of(hipError_t e, const char* what) { return device_status(e, what); }
-
 }  // namespace jfkv
 
 // ------------------------------------------------------------------ pool
@@ -568,17 +517,89 @@ jf_status jf_decode_step_q4_static(const jf_kv_layout* layout, const jf_kv_pool_
                        "decode launch (static scratch)");
 }
 
+namespace {
+
+// Sizes and scale of a prefill call.
+jf_status check_prefill_sizes(const jf_kv_layout* layout, int32_t T, int32_t num_q_heads,
+                              int32_t max_pages, int32_t prefix_len, float softmax_scale) {
+  if (T < 0 || prefix_len < 0 || num_q_heads <= 0 || max_pages < 0)
+    return fail(JF_ERR_INVALID, "negative size");
+  if (num_q_heads % layout->num_kv_heads)
+    return fail(JF_ERR_INVALID, "num_q_heads %d is not a multiple of num_kv_heads %d",
+                num_q_heads, layout->num_kv_heads);
+  if ((int64_t)prefix_len > (int64_t)max_pages * layout->page_size)
+    return fail(JF_ERR_INVALID, "prefix_len %d exceeds max_pages %d * page_size %d",
+                prefix_len, max_pages, layout->page_size);
+  if ((int64_t)prefix_len + T > INT32_MAX)
+    return fail(JF_ERR_INVALID, "prefix_len + T overflows int32");
+  if (!(softmax_scale == softmax_scale) || softmax_scale == INFINITY ||
+      softmax_scale == -INFINITY)
+    return fail(JF_ERR_INVALID, "softmax_scale must be finite");
+  return ok();
+}
+
+jf_status check_prefill(const jf_kv_layout* layout, const jf_kv_pool_ptrs* pool, const void* q,
+                        const void* k_chunk, const void* v_chunk, int32_t T, int32_t num_q_heads,
+                        const int32_t* block_table, int32_t max_pages, int32_t prefix_len,
+                        float softmax_scale, const void* out) {
+  jf_status st = check_layout(layout);
+  if (st) return st;
+  if ((st = check_pool(pool))) return st;
+  if ((st = check_prefill_sizes(layout, T, num_q_heads, max_pages, prefix_len, softmax_scale)))
+    return st;
+  if (T == 0) return ok();
+  if (!q || !k_chunk || !v_chunk || !out || (prefix_len > 0 && !block_table))
+    return fail(JF_ERR_INVALID, "NULL device pointer");
+  return ok();
+}
+
+}  // namespace
+
 jf_status jf_prefill_attn_q4(const jf_kv_layout* layout, const jf_kv_pool_ptrs* pool,
                              const void* q, const void* k_chunk, const void* v_chunk,
                              int32_t T, int32_t num_q_heads, const int32_t* block_table,
                              int32_t max_pages, int32_t prefix_len, float softmax_scale,
                              void* out, hipStream_t stream) {
-  jf_status st = jfkv::check_prefill(layout, pool, q, k_chunk, v_chunk, T, num_q_heads,
-                                     block_table, max_pages, prefix_len, softmax_scale, out);
+  jf_status st = check_prefill(layout, pool, q, k_chunk, v_chunk, T, num_q_heads, block_table,
+                               max_pages, prefix_len, softmax_scale, out);
   if (st || T == 0) return st;
-  return device_status(jfkv::launch_prefill(*layout, *pool, q, k_chunk, v_chunk, T,
-                                            num_q_heads, block_table, max_pages, prefix_len,
-                                            softmax_scale, out, stream),
+  const jfkv::PrefillPlan whole = jfkv::prefill::make_plan(*layout, T, num_q_heads, prefix_len, false);
+  return device_status(jfkv::launch_prefill(*layout, *pool, q, k_chunk, v_chunk, T, num_q_heads,
+                                            block_table, prefix_len, softmax_scale, whole, nullptr,
+                                            out, stream),
+                       "prefill launch");
+}
+
+jf_status jf_prefill_workspace_bytes(const jf_kv_layout* layout, int32_t T, int32_t num_q_heads,
+                                     int32_t prefix_len, size_t* bytes) {
+  jf_status st = check_layout(layout);
+  if (st) return st;
+  if ((st = check_prefill_sizes(layout, T, num_q_heads, INT32_MAX, prefix_len, 0.0f))) return st;
+  if (!bytes) return fail(JF_ERR_INVALID, "NULL output pointer");
+  *bytes = 0;
+  if (T)
+    *bytes = jfkv::prefill::plan_bytes(
+        *layout, jfkv::prefill::make_plan(*layout, T, num_q_heads, prefix_len, true));
+  return ok();
+}
+
+jf_status jf_prefill_attn_q4_ws(const jf_kv_layout* layout, const jf_kv_pool_ptrs* pool,
+                                const void* q, const void* k_chunk, const void* v_chunk,
+                                int32_t T, int32_t num_q_heads, const int32_t* block_table,
+                                int32_t max_pages, int32_t prefix_len, float softmax_scale,
+                                void* workspace, size_t workspace_bytes, void* out,
+                                hipStream_t stream) {
+  jf_status st = check_prefill(layout, pool, q, k_chunk, v_chunk, T, num_q_heads, block_table,
+                               max_pages, prefix_len, softmax_scale, out);
+  if (st || T == 0) return st;
+  const jfkv::PrefillPlan p = jfkv::prefill::make_plan(*layout, T, num_q_heads, prefix_len, true);
+  if (p.n_blk && (!workspace || ((uintptr_t)workspace & 15) ||
+                  workspace_bytes < jfkv::prefill::plan_bytes(*layout, p)))
+    return fail(JF_ERR_INVALID, "workspace NULL, not 16-byte aligned or smaller than "
+                                "jf_prefill_workspace_bytes()");
+  return device_status(jfkv::launch_prefill(*layout, *pool, q, k_chunk, v_chunk, T, num_q_heads,
+                                            block_table, prefix_len, softmax_scale, p, workspace,
+                                            out, stream),
                        "prefill launch");
 }
 

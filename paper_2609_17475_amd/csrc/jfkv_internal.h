@@ -83,23 +83,19 @@ hipError_t launch_page_runs(const jf_kv_layout& L, const jf_kv_pool_ptrs& pool,
                             const int32_t* block_table, int32_t first, int32_t count, void* buf,
                             bool unpack, hipStream_t stream);
 
+// How a prefill call's work is laid over the chip (jfkv_prefill_plan.h): row
+// blocks and key tiles of a KV head, and the blocks that share the tiles
+// evenly (0: one block per row block, and no workspace).
+struct PrefillPlan {
+  int64_t n_rb = 0, tiles = 0;
+  int n_blk = 0;
+};
+
 hipError_t launch_prefill(const jf_kv_layout& L, const jf_kv_pool_ptrs& pool,
                           const void* q, const void* k_chunk, const void* v_chunk,
                           int32_t T, int32_t num_q_heads,
-                          const int32_t* block_table, int32_t max_pages,
-                          int32_t prefix_len, float softmax_scale, void* out,
-                          hipStream_t stream);
-
-// Argument checks of the prefill entry points (which sit beside the kernel's
-// work plan), and the status of a message or of a launch.
-jf_status check_prefill(const jf_kv_layout* layout, const jf_kv_pool_ptrs* pool, const void* q,
-                        const void* k_chunk, const void* v_chunk, int32_t T, int32_t num_q_heads,
-                        const int32_t* block_table, int32_t max_pages, int32_t prefix_len,
-                        float softmax_scale, const void* out);
-jf_status check_prefill_shape(const jf_kv_layout* layout, int32_t T, int32_t num_q_heads,
-                              int32_t prefix_len);
-jf_status status_invalid(const char* message);
-jf_status status_of(hipError_t e, const char* what);
+                          const int32_t* block_table, int32_t prefix_len, float softmax_scale,
+                          const PrefillPlan& plan, void* ws, void* out, hipStream_t stream);
 
 hipError_t launch_tq4_encode(const jf_kv_layout& L, void* words, void* norms, const void* x,
                              const float* signs, const float* centroids, const int32_t* cu_tok,

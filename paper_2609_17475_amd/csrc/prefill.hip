@@ -37,7 +37,7 @@
 //
 // Block = 8 waves sharing KV head kv, 32 query rows per wave (16 at d = 256); a row is
 // (chunk position i, query head h of kv), position-major.  A block has one row
-// block, or (see PrefillPlan) an even share of its KV head's tiles whatever
+// block, or (see jfkv_prefill_plan.h) an even share of its KV head's tiles whatever
 // row blocks they belong to.  Per 64-key tile:
 //   S^T = K Q^T      (A = K code tile [key][dim] from LDS, B = Q^T in
 //                     registers, per scale group; a lane holds one query
@@ -57,39 +57,12 @@
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 
-#include <algorithm>
-
 #include "jfkv_internal.h"
-
-namespace jfkv {
-
-// Key tiles of the row blocks of one KV head in turn: block rb (rows rb * rows
-// .. of (position, query head) rows) has the prefix's n_pre tiles and those of
-// the chunk up to its last position.  Its last row over gq * kt is carried as
-// quotient and remainder, so stepping needs no division.
-struct RowBlockTiles {
-  int n_pre, last, q, r, dq, dr, u;
-  __host__ __device__ RowBlockTiles(int rows, int T, int gq, int n_pre_, int kt)
-      : n_pre(n_pre_), last((T - 1) / kt), u(gq * kt) {
-    q = (rows - 1) / u;
-    r = (rows - 1) % u;
-    dq = rows / u;
-    dr = rows % u;
-  }
-  __host__ __device__ int tiles() const { return n_pre + 1 + (q < last ? q : last); }
-  __host__ __device__ void next() {
-    q += dq;
-    r += dr;
-    if (r >= u) {
-      r -= u;
-      ++q;
-    }
-  }
-};
-
-}  // namespace jfkv
+#include "jfkv_prefill_plan.h"
 
 namespace {
+
+using namespace jfkv::prefill;
 
 typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 typedef _Float16 h2 __attribute__((ext_vector_type(2)));
@@ -97,18 +70,9 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr float kLog2e = 1.4426950408889634f;
-// Keys per tile (a page holds whole tiles): 64, or 32 at d = 256, where the
-// double-buffered K and two V tiles of 64 keys would not fit in LDS.
-template <int D>
-constexpr int keys_per_tile() { return D > 128 ? 32 : 64; }
 constexpr float kTau = 8.0f;       // lazy-rescale margin, log2 units
 constexpr float kMinit = -1e30f;   // initial running maximum (finite)
 constexpr float kFoldMax = 32768.0f;  // running maxima the bias product subtracts
-
-constexpr int kWaves = 8;          // waves per block: two per SIMD
-// 16-row MFMA tiles of query rows per wave (the registers of d = 256 hold one)
-template <int D>
-constexpr int row_tiles() { return D > 128 ? 1 : 2; }
 
 __device__ __forceinline__ h2 as_h2(uint32_t u) { return __builtin_bit_cast(h2, u); }
 __device__ __forceinline__ uint32_t as_u32(h2 v) { return __builtin_bit_cast(uint32_t, v); }
@@ -166,12 +130,6 @@ __device__ __forceinline__ void store_o4(__half* dst, f32x4 acc, float inv) {
   v.y = __builtin_bit_cast(uint32_t, __floats2half2_rn(acc[2] * inv, acc[3] * inv));
   *reinterpret_cast<uint2*>(dst) = v;
 }
-
-// fp32 words of a part of a row block in the workspace: per wave the output
-// accumulators ([dim tile][row tile][lane] of four), then (maximum, sum)
-// ([row tile][lane])
-template <int D>
-constexpr int part_floats() { return kWaves * row_tiles<D>() * 64 * (D / 4 + 2); }
 
 // PRE: the call has a prefix.  Without one (the first chunk of a prompt) no
 // tile is rebuilt from codes, so the registers of that hold the chunk rows of
@@ -240,7 +198,7 @@ __global__ __launch_bounds__(64 * kWaves) void prefill_kernel(
   if (ws) {
     j0 = blk * head_tiles / n_blk;
     left = (blk + 1) * head_tiles / n_blk - j0;
-    jfkv::RowBlockTiles rbt(kRows, T, gq, n_pre, KT);
+    RowBlockTiles rbt(kRows, T, gq, n_pre, KT);
     for (rb = 0; j0 >= rbt.tiles(); rbt.next(), ++rb) j0 -= rbt.tiles();
   }
 
@@ -853,7 +811,7 @@ __global__ __launch_bounds__(64 * SW * TW) void prefill_combine_kernel(
   const int r0 = rb * kRows + 16 * NR * rw;
   if (r0 / gq >= T) return;  // no rows
   const int n_pre = (prefix_len + KT - 1) / KT;
-  jfkv::RowBlockTiles rbt(kRows, T, gq, n_pre, KT);
+  RowBlockTiles rbt(kRows, T, gq, n_pre, KT);
   int base = 0;
   for (int i = 0; i < rb; ++i, rbt.next()) base += rbt.tiles();
   const int end = base + rbt.tiles();
@@ -933,100 +891,11 @@ __global__ __launch_bounds__(64 * SW * TW) void prefill_combine_kernel(
   }
 }
 
-// How a call's work is laid over the chip: n_blk blocks per KV head share the
-// head's `tiles` key tiles (over all its row blocks) evenly, or n_blk = 0: one
-// block per row block.  A block fills a CU, so row blocks that do not fill the
-// chip, or leave its last turn nearly empty, cost as much as if they did.
-// Row blocks are started in turn, later ones have more tiles, and a CU takes
-// the next when it is done, so its chain is row blocks i, i + CUs, ...; the
-// longest chain is the time of whole row blocks.
-// Shares of one tile pay while half the chip takes them, otherwise two tiles
-// and more (without a prefix, where tiles are shorter, four).  Against whole
-// row blocks an even share costs, in tiles (SplitCost): the combine's launch;
-// a query load, a pipeline fill and a state to store for each further row
-// block that it touches; and the states' traffic, in proportion to the blocks.
-// Fitted at 980 shapes of 16..8,192 rows, half of them without a prefix, the
-// others over 20..200,000 positions, at 64..8 heads of 64, 128 and 256 dims, of
-// both layouts each (a tile takes 3.0, 1.8 and 2.1 us at head_dim 128, 64 and
-// 256 with a prefix, 2.3, 1.3 and 1.4 without): the rule's choices cost 0.05 %
-// more than the faster layout of each shape, 5 % at most above 30 us.
-// Measured, even shares against whole row blocks: 256 rows over 196,608 (24/4
-// heads, 256) 2.50 against 13.1 ms; 1,000 over 7,000 (32/8, 128) 218 against
-// 392 us; 100 over 20,000 (4/1, 128) 37 against 1,010 us; 72 over 162 (4/1,
-// 128) 17 against 23 us; and where row blocks stay whole: 16 over 162 (4/1,
-// 128) 18.1 against 17.4 us; without a prefix, 4,096 of 32/8 heads, 128, 260
-// against 230, 2,509 of 64/8 256 against 183, 5,981 of 16/2, 64, 214 against 174.
-struct PrefillPlan {
-  int64_t n_rb = 0, tiles = 0;
-  int n_blk = 0;
-};
-struct SplitCost {
-  double combine, part, full;  // per call, per further row block touched, of states when they fill the chip
-};
-template <int D, bool PRE>
-constexpr SplitCost kSplitCost = D == 128 ? SplitCost{1, PRE ? 3 : 3.3, PRE ? 5 : 5.5}
-                                 : D == 64 ? (PRE ? SplitCost{4, 3, 2} : SplitCost{1, 4, 6})
-                                           : (PRE ? SplitCost{2, 8, 5.5} : SplitCost{0, 6, 5});
-// A split has to gain what its scratch, its second launch and the estimate's own
-// error are worth.  2,048 rows of 32/8 heads (two full turns): over 16,384
-// positions estimated at 2.1 % less, 874 against 897 us; over 32,768 1.1 % less,
-// 1,647 against 1,669; over 65,536 0.6 % less, 3,189 against 3,206; over 131,072
-// 0.3 % less, 6,291 against 6,283.
-constexpr double kWorthwhile = 0.98;
-constexpr int64_t kMaxTurns = 16;  // row blocks per CU above which the last turn hardly counts
-
-template <int D>
-PrefillPlan plan_t(const jf_kv_layout& L, int32_t T, int32_t Hq, int32_t prefix_len) {
-  constexpr int kRows = 16 * row_tiles<D>() * kWaves;
-  constexpr int KT = keys_per_tile<D>();
-  PrefillPlan p;
-  const int gq = Hq / L.num_kv_heads;
-  const int n_pre = (prefix_len + KT - 1) / KT;
-  p.n_rb = ((int64_t)T * gq + kRows - 1) / kRows;
-  const int64_t per_head = std::max(1, jfkv::num_cus() / L.num_kv_heads);
-  if (p.n_rb > kMaxTurns * per_head) return p;
-  // tiles of the two longest chains of row blocks on one CU: the last of those
-  // without and of those with a row block in the last turn
-  int64_t chain[2] = {0, 0};
-  jfkv::RowBlockTiles rbt(kRows, T, gq, n_pre, KT);
-  for (int64_t rb = 0; rb < p.n_rb; ++rb, rbt.next()) {
-    p.tiles += rbt.tiles();
-    if (rb % per_head == per_head - 1) chain[0] += rbt.tiles();
-    if (rb % per_head == (p.n_rb - 1) % per_head) chain[1] += rbt.tiles();
-  }
-  const int64_t whole = std::max(chain[0], chain[1]);
-  const int64_t n_blk =
-      n_pre ? std::max(std::min(p.tiles, per_head / 2), std::min(p.tiles / 2, per_head))
-            : std::min(p.tiles / 4, per_head);
-  if (n_blk <= 1) return p;
-  const int64_t share = (p.tiles + n_blk - 1) / n_blk;
-  // row blocks that a share touches: most where they are shortest, at the start
-  int64_t touched = 1, at = 0;
-  rbt = jfkv::RowBlockTiles(kRows, T, gq, n_pre, KT);
-  for (; touched <= p.n_rb && (at += rbt.tiles()) < share; rbt.next()) ++touched;
-  const SplitCost c = n_pre ? kSplitCost<D, true> : kSplitCost<D, false>;
-  const double cost = c.combine + c.part * (touched - 1) + c.full * n_blk / per_head;
-  if (share + cost < kWorthwhile * whole && (n_blk + 1) * p.tiles <= INT32_MAX)  // (the kernels' products)
-    p.n_blk = (int)n_blk;
-  return p;
-}
-
-PrefillPlan plan(const jf_kv_layout& L, int32_t T, int32_t Hq, int32_t prefix_len) {
-  return L.head_dim == 64    ? plan_t<64>(L, T, Hq, prefix_len)
-         : L.head_dim == 128 ? plan_t<128>(L, T, Hq, prefix_len)
-                             : plan_t<256>(L, T, Hq, prefix_len);
-}
-
-size_t plan_bytes(const jf_kv_layout& L, const PrefillPlan& p) {
-  const size_t part = L.head_dim == 64 ? part_floats<64>() : L.head_dim == 128 ? part_floats<128>() : part_floats<256>();
-  return 2 * (size_t)p.n_blk * L.num_kv_heads * part * sizeof(float);
-}
-
 template <int D, int G, bool PRE>
 hipError_t launch_t(const jf_kv_layout& L, const jf_kv_pool_ptrs& pool, const void* q,
                     const void* k_chunk, const void* v_chunk, int32_t T, int32_t Hq,
                     const int32_t* block_table, int32_t prefix_len, float softmax_scale, float* ws,
-                    const PrefillPlan& p, void* out, hipStream_t stream) {
+                    const jfkv::PrefillPlan& p, void* out, hipStream_t stream) {
   const int64_t blocks = (ws ? p.n_blk : p.n_rb) * L.num_kv_heads;
   hipLaunchKernelGGL((prefill_kernel<D, G, PRE>), dim3((uint32_t)blocks), dim3(64 * kWaves), 0, stream,
                      static_cast<const uint8_t*>(pool.k_codes),
@@ -1057,7 +926,7 @@ hipError_t launch_t(const jf_kv_layout& L, const jf_kv_pool_ptrs& pool, const vo
 hipError_t dispatch(const jf_kv_layout& L, const jf_kv_pool_ptrs& pool, const void* q,
                     const void* k_chunk, const void* v_chunk, int32_t T, int32_t Hq,
                     const int32_t* block_table, int32_t prefix_len, float softmax_scale, float* ws,
-                    const PrefillPlan& p, void* out, hipStream_t stream) {
+                    const jfkv::PrefillPlan& p, void* out, hipStream_t stream) {
 #define JF_PREFILL_CASE(D_, G_)                                                                  \
   if (L.head_dim == D_ && (prefix_len ? L.group_size == G_ : G_ == 32))                          \
     return prefix_len ? launch_t<D_, G_, true>(JF_PREFILL_ARGS)                                  \
@@ -1083,43 +952,10 @@ namespace jfkv {
 
 hipError_t launch_prefill(const jf_kv_layout& L, const jf_kv_pool_ptrs& pool, const void* q,
                           const void* k_chunk, const void* v_chunk, int32_t T, int32_t Hq,
-                          const int32_t* block_table, int32_t max_pages, int32_t prefix_len,
-                          float softmax_scale, void* out, hipStream_t stream) {
-  (void)max_pages;  // validated on the host: prefix_len <= max_pages * page_size
-  PrefillPlan p;
-  const int rows = 16 * kWaves * (L.head_dim > 128 ? row_tiles<256>() : row_tiles<128>());
-  p.n_rb = ((int64_t)T * (Hq / L.num_kv_heads) + rows - 1) / rows;
+                          const int32_t* block_table, int32_t prefix_len, float softmax_scale,
+                          const PrefillPlan& plan, void* ws, void* out, hipStream_t stream) {
   return dispatch(L, pool, q, k_chunk, v_chunk, T, Hq, block_table, prefix_len, softmax_scale,
-                  nullptr, p, out, stream);
+                  plan.n_blk ? static_cast<float*>(ws) : nullptr, plan, out, stream);
 }
 
 }  // namespace jfkv
-
-jf_status jf_prefill_workspace_bytes(const jf_kv_layout* layout, int32_t T, int32_t num_q_heads,
-                                     int32_t prefix_len, size_t* bytes) {
-  jf_status st = jfkv::check_prefill_shape(layout, T, num_q_heads, prefix_len);
-  if (st) return st;
-  if (!bytes) return jfkv::status_invalid("NULL output pointer");
-  *bytes = T ? plan_bytes(*layout, plan(*layout, T, num_q_heads, prefix_len)) : 0;
-  return JF_OK;
-}
-
-jf_status jf_prefill_attn_q4_ws(const jf_kv_layout* layout, const jf_kv_pool_ptrs* pool,
-                                const void* q, const void* k_chunk, const void* v_chunk,
-                                int32_t T, int32_t num_q_heads, const int32_t* block_table,
-                                int32_t max_pages, int32_t prefix_len, float softmax_scale,
-                                void* workspace, size_t workspace_bytes, void* out,
-                                hipStream_t stream) {
-  jf_status st = jfkv::check_prefill(layout, pool, q, k_chunk, v_chunk, T, num_q_heads,
-                                     block_table, max_pages, prefix_len, softmax_scale, out);
-  if (st || T == 0) return st;
-  const PrefillPlan p = plan(*layout, T, num_q_heads, prefix_len);
-  if (p.n_blk && (!workspace || ((uintptr_t)workspace & 15) || workspace_bytes < plan_bytes(*layout, p)))
-    return jfkv::status_invalid("workspace NULL, not 16-byte aligned or smaller than "
-                                "jf_prefill_workspace_bytes()");
-  return jfkv::status_of(dispatch(*layout, *pool, q, k_chunk, v_chunk, T, num_q_heads, block_table,
-                                  prefix_len, softmax_scale,
-                                  p.n_blk ? static_cast<float*>(workspace) : nullptr, p, out,
-                                  stream),
-                         "prefill launch");
-}

@@ -122,6 +122,39 @@ static void validation() {
   CHECK(jf_verify_attn_q4(&L, &pool, p, 1, 3, 32, ip, 4, ip, 1.0f, 8, p, ws, p, nullptr) == JF_ERR_INVALID);
   CHECK(jf_verify_attn_q4(&L, &pool, p, 1, 3, 32, ip, 4, ip, 1.0f, 8, p, 3 * ws, p, nullptr) == JF_OK);
   CHECK(jf_prefill_attn_q4(&L, &pool, p, p, p, 16, 32, ip, 4, 4 * 256 + 1, 1.0f, p, nullptr) == JF_ERR_INVALID);
+  CHECK(jf_prefill_attn_q4(&L, &pool, p, p, p, 16, 32, ip, 4, 4 * 256, 1.0f, p, nullptr) == JF_OK);
+  CHECK(jf_prefill_attn_q4(&L, &pool, p, p, nullptr, 16, 32, ip, 4, 0, 1.0f, p, nullptr) == JF_ERR_INVALID);
+  // ... and with a workspace: none needed, and one of exactly the bytes asked for
+  size_t pw = 1;
+  CHECK(jf_prefill_workspace_bytes(&L, 64, 32, 0, &pw) == JF_OK && pw == 0);
+  CHECK(jf_prefill_attn_q4_ws(&L, &pool, p, p, p, 64, 32, ip, 4, 0, 1.0f, nullptr, 0, p, nullptr) == JF_OK);
+  CHECK(jf_prefill_workspace_bytes(&L, 0, 32, 3000, &pw) == JF_OK && pw == 0);
+  CHECK(jf_prefill_workspace_bytes(&L, 20, 30, 3000, &pw) == JF_ERR_INVALID);
+  CHECK(jf_prefill_workspace_bytes(&L, -1, 32, 3000, &pw) == JF_ERR_INVALID);
+  CHECK(jf_prefill_workspace_bytes(nullptr, 20, 32, 3000, &pw) == JF_ERR_INVALID);
+  CHECK(jf_prefill_workspace_bytes(&L, 20, 32, 3000, nullptr) == JF_ERR_INVALID);
+  CHECK(jf_prefill_workspace_bytes(&L, 20, 32, 3000, &pw) == JF_OK && pw > 0);
+  std::vector<uint8_t> scratch(pw + 16);
+  uint8_t* sp = reinterpret_cast<uint8_t*>(((uintptr_t)scratch.data() + 15) & ~(uintptr_t)15);
+  auto split = [&](int32_t prefix, void* w, size_t n) {
+    return jf_prefill_attn_q4_ws(&L, &pool, p, p, p, 20, 32, ip, 12, prefix, 1.0f, w, n, p, nullptr);
+  };
+  CHECK(split(3000, sp, pw) == JF_OK);
+  CHECK(split(3000, sp, pw - 1) == JF_ERR_INVALID && std::strstr(jf_last_error(), "workspace"));
+  CHECK(split(3000, sp + 4, pw) == JF_ERR_INVALID);
+  CHECK(split(3000, nullptr, pw) == JF_ERR_INVALID);
+  CHECK(split(12 * 256 + 1, sp, pw) == JF_ERR_INVALID && std::strstr(jf_last_error(), "prefix_len"));
+  // plans over the whole range of sizes: bounded by two states per CU
+  std::mt19937 rng(5);
+  for (int i = 0; i < 4000; ++i) {
+    const int32_t d = 64 << rng() % 3, hkv = 1 + rng() % 40, gq = 1 + rng() % (rng() % 2 ? 16 : 4000);
+    const jf_kv_layout any = {256, hkv, d, 64, 16};
+    int32_t T = rng() >> (1 + rng() % 31), prefix = rng() >> (1 + rng() % 31);
+    if (i % 8 == 0) prefix = INT32_MAX - T;  // (the largest that is accepted)
+    const bool fits = (int64_t)T + prefix <= INT32_MAX;
+    CHECK(jf_prefill_workspace_bytes(&any, T, gq * hkv, prefix, &pw) == (fits ? JF_OK : JF_ERR_INVALID));
+    CHECK(!fits || pw <= (size_t)2 * 256 * 8 * 2 * 64 * (128 / 4 + 2) * 4);
+  }
   CHECK(jf_reconstruct_q4(&L, &pool, ip, 4, 100, 7, 2, p, p, nullptr) == JF_ERR_INVALID);
   CHECK(jf_reconstruct_q4(&L, &pool, ip, 4, 100, 6, 2, p, p, nullptr) == JF_OK);
   jf_kv_layout bad = {256, 8, 96, 32, 16};

@@ -16,6 +16,7 @@
 #include <vector>
 
 #include "jfkv_internal.h"
+#include "jfkv_prefill_plan.h"
 
 namespace {
 struct Range {
@@ -132,9 +133,12 @@ hipError_t launch_decode_static(const jf_kv_layout&, const jf_kv_pool_ptrs&, con
                                 int32_t, const int32_t*, float, int32_t, void*, hipStream_t) {
   return hipSuccess;
 }
-hipError_t launch_prefill(const jf_kv_layout&, const jf_kv_pool_ptrs&, const void*, const void*,
-                          const void*, int32_t, int32_t, const int32_t*, int32_t, int32_t, float,
-                          void*, hipStream_t) {
+int num_cus() { return 256; }
+// Writes the workspace of a split call over its whole length.
+hipError_t launch_prefill(const jf_kv_layout& L, const jf_kv_pool_ptrs&, const void*, const void*,
+                          const void*, int32_t, int32_t, const int32_t*, int32_t, float,
+                          const PrefillPlan& plan, void* ws, void*, hipStream_t) {
+  if (plan.n_blk) std::memset(ws, 0xA5, prefill::plan_bytes(L, plan));
   return hipSuccess;
 }
 hipError_t launch_reconstruct(const jf_kv_layout&, const jf_kv_pool_ptrs&, const int32_t*,
