@@ -29,6 +29,10 @@ def test_prefill_workspace_bytes_and_validation():
     for T, p0 in ((20, 3000), (256, 200000), (1000, 7000), (2049, 65536)):
         n = jfkv.jf_prefill_workspace_bytes(lay, T, 32, p0)
         assert 0 < n <= 2 * 256 * part and n % part == 0
+    # ... of 256 rows at head_dim 64 and 128 rows at 256
+    for d, part, mb in ((64, 256 * (64 + 8) * 4, 38), (128, part, 72), (256, 128 * (256 + 8) * 4, 70)):
+        n = jfkv.jf_prefill_workspace_bytes(jfkv.layout(256, 4, d, 64, 16), 300, 24, 200000)
+        assert 0 < n <= 2 * 256 * part <= mb * 10 ** 6 and n % part == 0
     with pytest.raises(jfkv.JfError):
         jfkv.jf_prefill_workspace_bytes(lay, 64, 30, 0)
     ptrs = jfkv.PoolPtrs(1, 1, 1, 1)
@@ -86,6 +90,67 @@ def test_split_prefill_matches_oracle_and_whole_row_blocks(P, hkv, hq, d, G, p0,
         return
     ref = oracle.prefill(case.host, q, kc, vc, table, p0, scale)
     log("  max err %.3e rel L2 %.3e" % check_tol(split.cpu().numpy(), ref, what="split", **tol))
+
+
+def _layout(hkv, hq, d, G, p0, T):
+    """Blocks per KV head and row blocks of a call (0 blocks: not split)."""
+    rows = 128 if d == 256 else 256
+    part = rows * (d + 4 * 2) * 4
+    n = jfkv.jf_prefill_workspace_bytes(jfkv.layout(64, hkv, d, G, 64), T, hq, p0)
+    return n // (2 * hkv * part), -(-T * (hq // hkv) // rows)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("P,hkv,hq,d,G,p0,T,form", [
+    # few parts per row block (the combine's first form), some (its second)
+    (64, 64, 64, 64, 32, 1500, 400, 1),
+    (64, 32, 64, 128, 32, 300, 390, 1),
+    (64, 8, 16, 256, 32, 200, 1100, 1),
+    (64, 2, 8, 64, 64, 700, 300, 2),
+    (64, 4, 8, 256, 64, 500, 300, 2),
+    # more row blocks than blocks: shares hold whole row blocks, whose rows are
+    # written by the block itself in the middle of a split call
+    (64, 64, 64, 64, 32, 200, 1100, 0),
+    (64, 32, 64, 256, 64, 400, 520, 0),
+    # no prefix, split and whole, odd numbers of rows
+    (64, 2, 8, 64, 32, 0, 1101, 1),
+    (64, 8, 8, 64, 64, 0, 1201, 1),
+    (64, 4, 8, 256, 64, 0, 701, 2),
+    (64, 1, 4, 256, 128, 0, 901, 2),
+    (64, 1, 4, 128, 32, 0, 1301, 1),
+    (64, 2, 8, 64, 64, 0, 151, None),
+    (64, 1, 2, 64, 32, 0, 65, None),
+    (64, 4, 24, 256, 64, 0, 101, None),
+    (64, 2, 8, 256, 32, 0, 77, None),
+])
+def test_split_prefill_forms_match_oracle(P, hkv, hq, d, G, p0, T, form):
+    """Every form of the split call and its combine at every head size, all rows
+    against the oracle.  form: 1 and 2, up to 4 and up to 16 parts per row block;
+    0, more row blocks than blocks; None, not split.
+
+    Tolerance: p is rounded to fp16, 2^-11 of itself at most, so an output moves
+    by at most 2^-11 sum p |v - o| beside its own rounding, 2^-11 |o|.  The values
+    are unit normals (no outlier channels: with those, |v - o| up to ~24, one of
+    the 1.6 million outputs of the first case is 5.6e-3 off, split or whole);
+    their mean distance from a weighted mean is below 2: 1e-3."""
+    import oracle
+    from gpu_cases import build, check_tol, log
+    n_blk, n_rb = _layout(hkv, hq, d, G, p0, T)
+    log("split prefill hkv=%d hq=%d d=%d G=%d p0=%d T=%d: %d blocks, %d row blocks" % (
+        hkv, hq, d, G, p0, T, n_blk, n_rb))
+    parts = n_blk // n_rb + 2
+    assert {None: n_blk == 0, 0: 0 < n_blk < n_rb, 1: n_blk >= n_rb and parts <= 4, 2: 4 < parts <= 16}[form]
+    case = build(P=P, hkv=hkv, d=d, G=G, hq=hq, lens=(p0 + T,), n_out=0, seed=p0 + T)
+    rng = np.random.default_rng(p0 * 3 + T)
+    kc, vc = (rng.standard_normal((T, hkv, d)).astype(np.float16) for _ in range(2))
+    q = (rng.standard_normal((T, hq, d)) / np.sqrt(d)).astype(np.float16)
+    args = [torch.from_numpy(x).cuda() for x in (q, kc, vc, case.tables[0])]
+    out = torch.full(q.shape, float("nan"), dtype=torch.float16, device="cuda")
+    jfkv.jf_prefill_attn_q4(case.gpu, *args, p0, 1.0, out)
+    torch.cuda.synchronize()
+    ref = oracle.prefill(case.host, q, kc, vc, case.tables[0], p0, 1.0)
+    log("  max err %.3e rel L2 %.3e" % check_tol(out.cpu().numpy(), ref, atol=1e-3, rel_elem=2.0 ** -11,
+                                                 rel_l2=1e-3, what="split"))
 
 
 def _call(P, hkv, hq, d, G, p0, T):
