@@ -59,15 +59,18 @@ struct RowBlockTiles {
 // the next when it is done, so its chain is row blocks i, i + CUs, ...; the
 // longest chain is the time of whole row blocks.
 // Shares of one tile pay while half the chip takes them, otherwise two tiles
-// and more (without a prefix, where tiles are shorter, four).  Against whole
-// row blocks an even share costs, in tiles (SplitCost): the combine's launch;
-// a query load, a pipeline fill and a state to store for each further row
-// block that it touches; and the states' traffic, in proportion to the blocks.
-// Fitted at 980 shapes of 16..8,192 rows, half of them without a prefix, the
-// others over 20..200,000 positions, at 64..8 heads of 64, 128 and 256 dims, of
-// both layouts each (a tile takes 3.0, 1.8 and 2.1 us at head_dim 128, 64 and
-// 256 with a prefix, 2.3, 1.3 and 1.4 without): the rule's choices cost 0.05 %
-// more than the faster layout of each shape, 5 % at most above 30 us.
+// and more (without a prefix, where tiles are shorter, four).  An even share
+// takes its tiles and, in tiles too (SplitCost), a query load, a pipeline fill
+// and a state to store for each further row block that it touches, and (with a
+// prefix, where chunk rows are not fetched ahead) more for chunk tiles; the
+// call takes its longest share, the combine's launch, and the states' traffic in
+// proportion to the blocks.
+// Fitted at 1,830 shapes of 16..8,192 rows, a third of them without a prefix,
+// the others over 1..200,000 positions, with 4 to 64 query heads of 64, 128 and
+// 256 dims, each laid out both ways (a tile takes 3.0, 1.8 and 2.1 us at
+// head_dim 128, 64 and 256 with a prefix, 2.3, 1.3 and 1.4 without): the rule's
+// choices cost 0.06 % more than the faster layout of each shape, 4 us at most
+// below 35 us and 6 % at most above.
 // Measured, even shares against whole row blocks: 256 rows over 196,608 (24/4
 // heads, 256) 2.50 against 13.1 ms; 1,000 over 7,000 (32/8, 128) 218 against
 // 392 us; 100 over 20,000 (4/1, 128) 37 against 1,010 us; 72 over 162 (4/1,
@@ -75,17 +78,20 @@ struct RowBlockTiles {
 // 128) 18.1 against 17.4 us; without a prefix, 4,096 of 32/8 heads, 128, 260
 // against 230, 2,509 of 64/8 256 against 183, 5,981 of 16/2, 64, 214 against 174.
 struct SplitCost {
-  double combine, part, full;  // per call, per further row block touched, of states when they fill the chip
+  double combine;  // per call
+  double part;     // per further row block that a share touches
+  double full;     // of the states, when the blocks fill the chip
+  double chunk;    // more per chunk tile of a share
 };
 template <int D, bool PRE>
-constexpr SplitCost kSplitCost = D == 128 ? SplitCost{1, PRE ? 3 : 3.3, PRE ? 5 : 5.5}
-                                 : D == 64 ? (PRE ? SplitCost{4, 3, 2} : SplitCost{1, 4, 6})
-                                           : (PRE ? SplitCost{2, 8, 5.5} : SplitCost{0, 6, 5});
+constexpr SplitCost kSplitCost = D == 128  ? (PRE ? SplitCost{1, 2.3, 3, 0.06} : SplitCost{0.2, 3.8, 6.3, 0})
+                                 : D == 64 ? (PRE ? SplitCost{4.7, 2, 0.8, 0.36} : SplitCost{0.9, 4.5, 7.1, 0})
+                                           : (PRE ? SplitCost{2.5, 3.6, 2, 0.37} : SplitCost{7.6, 7.6, 0.7, 0});
 // A split has to gain what its scratch, its second launch and the estimate's own
 // error are worth.  2,048 rows of 32/8 heads (two full turns): over 16,384
-// positions estimated at 2.1 % less, 874 against 897 us; over 32,768 1.1 % less,
-// 1,647 against 1,669; over 65,536 0.6 % less, 3,189 against 3,206; over 131,072
-// 0.3 % less, 6,291 against 6,283.
+// positions estimated at 2.7 % less, 874 against 897 us; over 32,768 1.4 % less,
+// 1,647 against 1,669; over 65,536 0.7 % less, 3,189 against 3,206; over 131,072
+// 0.4 % less, 6,291 against 6,283.
 constexpr double kWorthwhile = 0.98;
 constexpr int64_t kMaxTurns = 16;  // row blocks per CU above which the last turn hardly counts
 
@@ -114,14 +120,23 @@ PrefillPlan plan_t(const jf_kv_layout& L, int32_t T, int32_t Hq, int32_t prefix_
       n_pre ? std::max(std::min(p.tiles, per_head / 2), std::min(p.tiles / 2, per_head))
             : std::min(p.tiles / 4, per_head);
   if (n_blk <= 1) return p;
-  const int64_t share = (p.tiles + n_blk - 1) / n_blk;
-  // row blocks that a share touches: most where they are shortest, at the start
-  int64_t touched = 1, at = 0;
-  rbt = RowBlockTiles(kRows, T, gq, n_pre, KT);
-  for (; touched <= p.n_rb && (at += rbt.tiles()) < share; rbt.next()) ++touched;
   const SplitCost c = n_pre ? kSplitCost<D, true> : kSplitCost<D, false>;
-  const double cost = c.combine + c.part * (touched - 1) + c.full * n_blk / per_head;
-  if (share + cost < kWorthwhile * whole && (n_blk + 1) * p.tiles <= INT32_MAX)  // (the kernels' products)
+  const double tile = 1 + c.chunk * (p.tiles - p.n_rb * n_pre) / p.tiles;
+  double longest = 0;  // share
+  rbt = RowBlockTiles(kRows, T, gq, n_pre, KT);
+  int64_t end = rbt.tiles();  // of the row blocks up to rbt's
+  for (int64_t j = 0; j < n_blk; ++j) {
+    const int64_t from = j * p.tiles / n_blk, to = (j + 1) * p.tiles / n_blk;
+    int more = 0;
+    for (; end < to; ++more) {
+      rbt.next();
+      end += rbt.tiles();
+      if (end - rbt.tiles() <= from) --more;  // (the share begins with this row block)
+    }
+    longest = std::max(longest, (to - from) * tile + c.part * more);
+  }
+  const double split_time = longest + c.combine + c.full * n_blk / per_head;
+  if (split_time < kWorthwhile * whole && (n_blk + 1) * p.tiles <= INT32_MAX)  // (the kernels' products)
     p.n_blk = (int)n_blk;
   return p;
 }

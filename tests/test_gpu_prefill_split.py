@@ -110,7 +110,7 @@ def _layout(hkv, hq, d, G, p0, T):
     (64, 4, 8, 256, 64, 500, 300, 2),
     # more row blocks than blocks: shares hold whole row blocks, whose rows are
     # written by the block itself in the middle of a split call
-    (64, 64, 64, 64, 32, 200, 1100, 0),
+    (64, 32, 64, 64, 32, 400, 1100, 0),
     (64, 32, 64, 256, 64, 400, 520, 0),
     # no prefix, split and whole, odd numbers of rows
     (64, 2, 8, 64, 32, 0, 1101, 1),

@@ -41,6 +41,9 @@ def test_whole_row_blocks_where_a_split_costs_more(hq, hkv, d, group, T, prefix)
     (16, 2, 64, 32, 2048, 32768),    # 556 / 1,094
     (32, 8, 128, 64, 3072, 32768),   # 2,531 / 3,394
     (32, 8, 128, 64, 2048, 16384),   # 874 / 897
+    (32, 8, 128, 64, 2048, 64),      # 120 / 130
+    (40, 8, 128, 64, 2048, 86),      # 141 / 161
+    (24, 4, 256, 64, 1792, 216),     # 163 / 189
     (24, 4, 256, 64, 2048, 8192),    # 995 / 1,299
 ])
 def test_split_where_it_pays(hq, hkv, d, group, T, prefix):
@@ -55,3 +58,10 @@ def test_sizes_the_python_entry_does_not_ask_about_are_whole(hq, hkv, d):
              if not jfkv._prefill_scratch_bytes(jfkv.layout(256, hkv, d, 64, 4000), T, hq, p)]
     assert (64, 0) in asked and (1, 63) in asked
     assert not any(splits(hq, hkv, d, 64, T, p) for T, p in asked)
+
+
+@pytest.mark.parametrize("T,prefix", [(273, 19), (276, 3), (269, 21)])
+def test_shares_across_row_blocks_are_counted(T, prefix):
+    """Sixteen shares of five row blocks of two to six tiles: some begin in one row
+    block and end in the next (32 us against 27 with whole row blocks)."""
+    assert not splits(32, 8, 128, 64, T, prefix)
