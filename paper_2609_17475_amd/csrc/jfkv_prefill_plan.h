@@ -109,11 +109,16 @@ PrefillPlan plan_t(const jf_kv_layout& L, int32_t T, int32_t Hq, int32_t prefix_
   // tiles of the two longest chains of row blocks on one CU: the last of those
   // without and of those with a row block in the last turn
   int64_t chain[2] = {0, 0};
+  const int64_t last = (p.n_rb - 1) % per_head;
   RowBlockTiles rbt(kRows, T, gq, n_pre, KT);
-  for (int64_t rb = 0; rb < p.n_rb; ++rb, rbt.next()) {
-    p.tiles += rbt.tiles();
-    if (rb % per_head == per_head - 1) chain[0] += rbt.tiles();
-    if (rb % per_head == (p.n_rb - 1) % per_head) chain[1] += rbt.tiles();
+  for (int64_t rb = 0, cu = 0; rb < p.n_rb; ++rb, rbt.next()) {
+    const int t = rbt.tiles();
+    p.tiles += t;
+    if (cu == last) chain[1] += t;
+    if (++cu == per_head) {
+      cu = 0;
+      chain[0] += t;
+    }
   }
   const int64_t whole = std::max(chain[0], chain[1]);
   const int64_t n_blk =
@@ -122,21 +127,29 @@ PrefillPlan plan_t(const jf_kv_layout& L, int32_t T, int32_t Hq, int32_t prefix_
   if (n_blk <= 1) return p;
   const SplitCost c = n_pre ? kSplitCost<D, true> : kSplitCost<D, false>;
   const double tile = 1 + c.chunk * (p.tiles - p.n_rb * n_pre) / p.tiles;
-  double longest = 0;  // share
+  const double fixed = c.combine + c.full * n_blk / per_head, limit = kWorthwhile * whole;
+  const int64_t share = p.tiles / n_blk, rest = p.tiles % n_blk;
+  if (share * tile + fixed >= limit) return p;
+  // share j is tiles j * tiles / n_blk .. (j + 1) * tiles / n_blk - 1
+  double longest = 0;
   rbt = RowBlockTiles(kRows, T, gq, n_pre, KT);
   int64_t end = rbt.tiles();  // of the row blocks up to rbt's
-  for (int64_t j = 0; j < n_blk; ++j) {
-    const int64_t from = j * p.tiles / n_blk, to = (j + 1) * p.tiles / n_blk;
+  for (int64_t j = 0, to = 0, part = 0; j < n_blk; ++j) {
+    const int64_t from = to;
+    to += share;
+    if ((part += rest) >= n_blk) {
+      part -= n_blk;
+      ++to;
+    }
     int more = 0;
-    for (; end < to; ++more) {
+    while (end < to) {
+      more += end > from;  // (or the share begins with the next row block)
       rbt.next();
       end += rbt.tiles();
-      if (end - rbt.tiles() <= from) --more;  // (the share begins with this row block)
     }
     longest = std::max(longest, (to - from) * tile + c.part * more);
   }
-  const double split_time = longest + c.combine + c.full * n_blk / per_head;
-  if (split_time < kWorthwhile * whole && (n_blk + 1) * p.tiles <= INT32_MAX)  // (the kernels' products)
+  if (longest + fixed < limit && (n_blk + 1) * p.tiles <= INT32_MAX)  // (the kernels' products)
     p.n_blk = (int)n_blk;
   return p;
 }
