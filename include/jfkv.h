@@ -356,7 +356,7 @@ jf_status jf_prefill_attn_q4(const jf_kv_layout* layout,
  * jf_prefill_workspace_bytes gives the bytes such a call needs: 0 where the
  * work is even as it is (the workspace is then not used and may be NULL), and
  * never more than two partial states per compute unit, whatever the lengths
- * (73 MB at head_dim 128, 147 MB at 256).
+ * (on 256 of them 38 MB at head_dim 64, 71 MB at 128, 69 MB at 256).
  *   workspace  device scratch, 16-byte aligned, of at least that many bytes;
  *              its contents do not matter before the call nor after it.  Calls
  *              that may overlap in time must not share one.

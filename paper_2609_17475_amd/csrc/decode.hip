@@ -481,7 +481,9 @@ __device__ void combine_splits(const float* ws, __half* out, int b, int Hq, int 
 //
 // RING: stages of a wave's ring (at most).  A block with rings of three fills
 // a CU; with two (kPairStages), two blocks share one, and one's start, merge
-// and combine pass under the other's page loop (see launch_cs for when).
+// and combine pass under the other's page loop (see launch_cs for when).  At
+// d = 128 four waves per SIMD leave 128 registers, for which the fused step
+// spills 6.
 template <int D, int G, bool APPEND, int CS, int RING>
 __global__ __launch_bounds__(kMaxThreads, RING == kPairStages && D == 128 ? 4 : 1) void decode_kernel(
     uint8_t* __restrict__ k_codes, uint32_t* __restrict__ k_meta,

@@ -192,7 +192,11 @@ __global__ __launch_bounds__(64 * kWaves) void prefill_kernel(
   // of all the tiles of its KV head, row block after row block (the head's
   // tiles dealt evenly to n_blk blocks); rb, j0: the first one.  (One kernel
   // for both: with the split a template argument, the whole-row-block instance
-  // came out 8 % slower, 3.51 against 3.20 ms for 2,048 rows over 65,536.)
+  // came out 8 % slower, 3.51 against 3.20 ms for 2,048 rows over 65,536.  What
+  // the loop over row blocks keeps live costs registers: 31 are spilled at
+  // head_dim 128 and 2 at 256, 13-16 and 0 in a kernel of one row block, most of
+  // them outside the tile loop, where nine reloads per tile stand against four.
+  // Whole row blocks take 0-0.5 % longer for it, 3.21-3.24 against 3.20-3.23 ms.)
   int rb = blk, j0 = 0;
   int left = 1;  // tiles of the share from (rb, j0) on
   if (ws) {

@@ -13,7 +13,7 @@
 // What bounds the kernels: vector issue, then HBM.  Per vector ~80 vector
 // instructions and 4 LDS reads (~146 and ~25 with a lane per four elements).
 // K and V of 262,143 rows of 4 heads: 460 -> 314 us (2.9 -> 4.3 TB/s);
-// reconstruction of 2 heads over 196,608 positions: 169 -> 111 us (3.0 -> 4.5
+// reconstruction of 2 heads over 196,608 positions: 169 -> 108 us (3.0 -> 4.7
 // TB/s; a large copy reaches 5.1).
 //
 // Index of a coordinate: the number of midpoint thresholds between adjacent
@@ -413,10 +413,11 @@ hipError_t launch_tq4_encode(const jf_kv_layout& L, void* words, void* norms, co
                              const int32_t* start_pos, const int32_t* block_tables, int32_t B,
                              int32_t max_pages, int32_t total_tok, hipStream_t stream) {
   const int64_t n_vec = (int64_t)total_tok * L.num_kv_heads;
-  // persistent: at most kBlocksPerCu blocks per CU, whose waves take batches in
-  // turn (each block builds the bucket table once; 5, 6, 8 and 12 blocks: 327,
-  // 321, 314 and 312 us for the append above, 37.1, 36.6, 36.7 and 38.5 us for
-  // 20,000 rows)
+  // at most kBlocksPerCu blocks per CU, whose waves take batches in turn (each
+  // block builds the bucket table once).  Six of them are on the CU at a time (73
+  // registers); the other two start as those end, which evens the end out.  5, 6,
+  // 8 and 12 blocks: 327, 321, 314 and 312 us for the append above, 37.1, 36.6,
+  // 36.7 and 38.5 us for 20,000 rows.
   constexpr int kPerBlock = kWavesPerBlock * kBatch;
   constexpr int64_t kBlocksPerCu = 8;
   const int64_t need = (n_vec + kPerBlock - 1) / kPerBlock;
