@@ -222,7 +222,7 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void tq4_encode_kernel(
         e[h][2 * i] = add_halves(w);
         e[h][2 * i + 1] = sub_halves(w);
         float& q = ss[h][i >> 1];
-        q = add_squares(w, (i & 1) ? q : 0.0f);
+        q = add_squares(raw[h][i], (i & 1) ? q : 0.0f);
       }
     }
     if (more) load(batch + W);  // the registers are free; it returns during the transform

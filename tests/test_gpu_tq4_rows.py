@@ -11,6 +11,7 @@ import torch
 pytestmark = pytest.mark.gpu
 
 from gpu_cases import log  # noqa: E402
+from oracle import tq4  # noqa: E402
 from paper_2609_17475_amd import jfkv  # noqa: E402
 from test_gpu_tq4_decode import Case  # noqa: E402
 from test_gpu_reconstruct import test_tq4_reconstruct_matches_oracle as check_reconstruct  # noqa: E402
@@ -56,3 +57,21 @@ def test_cancelled_sums_are_positive_zeros(index):
         assert np.all(np.abs(got[:, 0] - s[0] * 16 * np.float64(c.c[index])) <= 2e-3 * 16 * abs(c.c[index]))
         assert not np.any(got[:, 1:]), what
         assert np.array_equal(np.signbit(got[:, 1:]), np.broadcast_to(s[1:] < 0, got[:, 1:].shape)), what
+
+
+def test_nan_rows_keep_the_norm_s_bits():
+    """The norm of a row with a NaN is that NaN, quiet, with its sign (the signs of
+    the transform do not enter the squares)."""
+    log("tq4 NaN rows")
+    lay = jfkv.layout(64, 4, 256, 64, 2)
+    x = torch.randn((16, 4, 256), generator=torch.Generator().manual_seed(1)).half()
+    for i in range(16):
+        x[i, :, 16 * i + i % 5] = float("nan")
+    pool = jfkv.TQ4Pool(lay, fill=0)
+    i32 = dict(dtype=torch.int32, device="cuda")
+    signs = torch.where(torch.arange(256) % 3 == 0, -1.0, 1.0).cuda()
+    jfkv.jf_tq4_encode_append(pool, x.cuda(), signs, Case(64, 1, (1,), 1).dev["c"],
+                              torch.tensor([0, 16], **i32), torch.tensor([0], **i32),
+                              torch.tensor([[1]], **i32))
+    bits = pool.norms.view(torch.int16)[1, :, :16].cpu().numpy().view(np.uint16)
+    assert np.all(bits == 0x7E00), bits
