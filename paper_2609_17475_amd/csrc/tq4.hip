@@ -368,9 +368,12 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void tq4_reconstruct_kernel(
       }
     fwht_from1(e, rl);
     // the lane holds rl.sign times the transform, but sums that cancel are +0
-    // in every lane: mul_pz keeps them so, and a zero's sign is then that of
-    // its element's sign, whatever the lane
-    const float f = rl.sign * rho[v] * 0.0625f;
+    // in every lane: mul_pz keeps them so, and the sign of a zero does not depend
+    // on the lane.  (A norm of 0 enters as the smallest fp32, whose products
+    // round to zeros of their signs.)
+    float f = rho[v] * 0.0625f;
+    if (f == 0.0f) f = copysignf(__FLT_DENORM_MIN__, f);
+    f *= rl.sign;
     u32x4 o[2];
 #pragma unroll
     for (int h = 0; h < 2; ++h)

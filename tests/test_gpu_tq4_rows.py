@@ -59,6 +59,34 @@ def test_cancelled_sums_are_positive_zeros(index):
         assert np.array_equal(np.signbit(got[:, 1:]), np.broadcast_to(s[1:] < 0, got[:, 1:].shape)), what
 
 
+@pytest.mark.parametrize("index", [None, 1, 14])
+def test_zero_norm_gives_zeros_of_the_vector_s_signs(index):
+    """A norm of 0 (a zero vector; all indices equal, as the encoder stores it, or
+    any) times the transform: zeros with the signs of the products, sums that
+    cancel counting as +0."""
+    log("tq4 zero norms, index %s" % index)
+    P, L = 64, 37
+    c = Case(P, 1, (L,), seed=5)
+    for pool in (c.k_pool, c.v_pool):
+        if index is not None:
+            pool.words.fill_(index * 0x11111111 - (1 << 32 if index > 7 else 0))
+        pool.norms.fill_(0.0)
+    k, v = (torch.full((1, L, 256), float("nan"), dtype=torch.float16, device="cuda") for _ in range(2))
+    jfkv.jf_tq4_reconstruct(c.k_pool, c.v_pool, c.dev["sk"], c.dev["sv"], c.dev["c"],
+                            torch.from_numpy(c.tables[0]).to("cuda"), L, 0, 1, k, v)
+    for what, got, pool, s in (("K", k, c.k_pool, c.sk), ("V", v, c.v_pool, c.sv)):
+        got = got.cpu().numpy()[0]
+        assert not np.any(got), what
+        words, _ = tq4.gather(pool.words.cpu().numpy().view(np.uint32), c.kn, c.tables[0], L)
+        x = tq4.reconstruct(tq4.unpack(words[:, 0]), np.ones(L, np.float16), s, c.c)
+        # sums near zero may have either sign in fp32 (2^-20 of the largest is far
+        # above their rounding, 8 * 2^-24); exact ones are +0, times the sign
+        sure = np.abs(x) > 2.0 ** -20 * np.abs(x).max()
+        assert np.array_equal(np.signbit(got)[sure], (x < 0)[sure]), what
+        if index is not None:
+            assert np.array_equal(np.signbit(got[:, 1:]), np.broadcast_to(s[1:] < 0, (L, 255))), what
+
+
 def test_nan_rows_keep_the_norm_s_bits():
     """The norm of a row with a NaN is that NaN, quiet, with its sign (the signs of
     the transform do not enter the squares)."""
