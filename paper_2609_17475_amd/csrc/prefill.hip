@@ -196,7 +196,8 @@ __global__ __launch_bounds__(64 * kWaves) void prefill_kernel(
   // the loop over row blocks keeps live costs registers: 31 are spilled at
   // head_dim 128 and 2 at 256, 13-16 and 0 in a kernel of one row block, most of
   // them outside the tile loop, where nine reloads per tile stand against four.
-  // Whole row blocks take 0-0.5 % longer for it, 3.21-3.24 against 3.20-3.23 ms.)
+  // Whole row blocks take 0-1 % longer for it: 2,048 rows over 32,768, groups of
+  // 128, 1,576-1,581 against 1,558-1,566 us; over 65,536, 64, 3,182-3,202 both.)
   int rb = blk, j0 = 0;
   int left = 1;  // tiles of the share from (rb, j0) on
   if (ws) {
@@ -757,6 +758,13 @@ __global__ __launch_bounds__(64 * kWaves) void prefill_kernel(
     // ---- a part of the row block's tiles: the unnormalized state, as it lies
     // in the registers, into one of the block's two slots (a share has at
     // most one part that ends its row block and one that begins it)
+    // (hidden from the compiler at head_dim 128 with groups of 64 and more, so
+    // that the rows' divisions after the tiles are not prepared before them:
+    // 2,048 rows of 32/8 heads over 32,768 positions 1,607-1,614 -> 1,588-1,593 us
+    // with groups of 128, over 65,536 3,206-3,247 -> 3,182-3,234 with 64.  With
+    // groups of 32 the tile loop came out 10 % slower for it, at 64 and 256 as fast.)
+    int gq_o = gq;
+    if constexpr (PRE && D == 128 && G >= 64) asm volatile("" : "+s"(gq_o));
     if (j1 - j0 < n_tiles) {
       float* rec = ws + (size_t)(2 * blockIdx.x + (j0 == 0)) * part_floats<D>() +
                    wave * (part_floats<D>() / kWaves);
@@ -775,13 +783,13 @@ __global__ __launch_bounds__(64 * kWaves) void prefill_kernel(
     #pragma unroll
       for (int n = 0; n < NR; ++n) {
         const int r = r0 + kRowsPerWave * wave + 16 * n + l16;
-        const int i = r / gq, hh = r % gq;
+        const int i = r / gq_o, hh = r % gq_o;
         // the row's sum: the four lanes of a query column hold disjoint keys
         float l = l_run[n] + __shfl_xor(l_run[n], 16);
         l += __shfl_xor(l, 32);
         if (i >= T) continue;
         const float inv = (l > 0.0f) ? 2.0f / l : 0.0f;  // (the value tiles hold V / 2)
-        __half* dst = out + ((size_t)i * Hq + kv * gq + hh) * D;
+        __half* dst = out + ((size_t)i * Hq + kv * gq_o + hh) * D;
     #pragma unroll
         for (int t = 0; t < DT; ++t) {
           const int d0 = 16 * t + 4 * q4;
